@@ -168,7 +168,8 @@ def valid_taps(kernels, L):
 
 def source_digest():
     h = hashlib.sha256()
-    for name in ("transform.hip", "plan.cpp", "rocket_internal.h", "minirocket.cpp"):
+    for name in ("transform.hip", "split.hip", "tiles.h", "plan.cpp", "plan_split.cpp", "rocket_internal.h",
+                 "minirocket.cpp"):
         with open(os.path.join(ROOT, "paper_2601_17091_amd", "csrc", name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()[:16]

@@ -18,7 +18,7 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB = os.path.join(HERE, "librocket.so")
 CHECKED_LIB = os.path.join(HERE, "librocket_checked.so")
-SOURCES = ["transform.hip", "plan.cpp", "generate.cpp", "minirocket.cpp"]
+SOURCES = ["transform.hip", "split.hip", "plan.cpp", "plan_split.cpp", "generate.cpp", "minirocket.cpp"]
 ARCH = "gfx950"
 
 
@@ -55,7 +55,7 @@ def compile_flags() -> list[str]:
 
 def build(verbose: bool = False) -> str:
     """Compile every source and link librocket.so, and the checked build
-    librocket_checked.so (transform.hip with ROCKET_CHECKED=1: device-side
+    librocket_checked.so (the .hip sources with ROCKET_CHECKED=1: device-side
     bounds checks for debugging); always rebuilds.  The compilations run in
     parallel."""
     os.makedirs(os.path.join(HERE, "_build"), exist_ok=True)
@@ -63,7 +63,7 @@ def build(verbose: bool = False) -> str:
     objs = {False: [], True: []}
     for checked in (False, True):
         for src in SOURCES:
-            if checked and src != "transform.hip":
+            if checked and not src.endswith(".hip"):
                 objs[True].append(os.path.join(HERE, "_build", src + ".o"))
                 continue
             obj = os.path.join(HERE, "_build", src + (".checked.o" if checked else ".o"))

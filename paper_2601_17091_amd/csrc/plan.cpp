@@ -157,34 +157,44 @@ rocket_status validate_kernels(const rocket_kernels *k, int32_t L) {
 
 static int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-void build_item_orders(HostPlan &P) {
+void order_items(const std::vector<int32_t> &variant, const std::vector<int32_t> &cost, int n_variants,
+                 std::vector<int32_t> &order, std::vector<int32_t> &split_begin,
+                 std::vector<int32_t> &layout_off) {
     // per variant, largest cost first (longest-processing-time first), dealt
     // to splits greedily by accumulated cost
-    std::vector<int32_t> by_cost(P.items.size());
+    std::vector<int32_t> by_cost(variant.size());
     for (size_t i = 0; i < by_cost.size(); ++i) by_cost[i] = (int32_t)i;
-    std::stable_sort(by_cost.begin(), by_cost.end(),
-                     [&](int32_t a, int32_t b) { return P.items[a].cost > P.items[b].cost; });
+    std::stable_sort(by_cost.begin(), by_cost.end(), [&](int32_t a, int32_t b) { return cost[a] > cost[b]; });
     for (int li = 0; li < kNumSplitLayouts; ++li) {
         const int ns = kSplitCounts[li];
-        P.layout_off.push_back((int32_t)P.split_begin.size());
-        for (int v = 0; v < P.n_variants; ++v) {
+        layout_off.push_back((int32_t)split_begin.size());
+        for (int v = 0; v < n_variants; ++v) {
             std::vector<std::vector<int32_t>> lists(ns);
             std::vector<int64_t> load(ns, 0);
             for (int32_t it : by_cost) {
-                if (P.items[it].variant != v) continue;
+                if (variant[it] != v) continue;
                 int best = 0;
                 for (int sp = 1; sp < ns; ++sp)
                     if (load[sp] < load[best]) best = sp;
                 lists[best].push_back(it);
-                load[best] += P.items[it].cost;
+                load[best] += cost[it];
             }
             for (int sp = 0; sp < ns; ++sp) {
-                P.split_begin.push_back((int32_t)P.order.size());
-                P.order.insert(P.order.end(), lists[sp].begin(), lists[sp].end());
+                split_begin.push_back((int32_t)order.size());
+                order.insert(order.end(), lists[sp].begin(), lists[sp].end());
             }
         }
-        P.split_begin.push_back((int32_t)P.order.size());
+        split_begin.push_back((int32_t)order.size());
     }
+}
+
+void build_item_orders(HostPlan &P) {
+    std::vector<int32_t> variant, cost;
+    for (const ItemDesc &it : P.items) {
+        variant.push_back(it.variant);
+        cost.push_back(it.cost);
+    }
+    order_items(variant, cost, P.n_variants, P.order, P.split_begin, P.layout_off);
 }
 
 // Toeplitz items (variants kToepVariant0..): the one (sigma = 4) or two

@@ -1,0 +1,379 @@
+// Host-side planning of split items: kernels grouped by dilation into items
+// of up to 32 rows, their weights split into bf16 parts and packed as MFMA A
+// fragments.  Pure host code; no HIP calls.
+#include <algorithm>
+#include <array>
+#include <cmath>
+#include <cstring>
+#include <map>
+#include <new>
+#include <utility>
+#include <vector>
+
+#include "rocket_internal.h"
+
+namespace rocket {
+
+// What a 32-column tile costs by variant, an edge tile more, and an item's
+// reductions and stores per series.  The split kernel runs at the card's power
+// limit (its clock falls to 1.6-1.75 GHz), so these are time at the limit in
+// 2.4 GHz cycles per SIMD: a 32x32x16 MFMA on random data 43, a vector
+// instruction 1.9, an LDS read 4.6 (each measured in a loop on all CUs).
+// Sweeps of the three rates by 10 % and of the edge and item terms from 0 to
+// twice moved passes over 30,000 x 1,000, 1,000 x 500 and 1,000 x 16,384
+// samples by less than 1 %.
+static constexpr double kTileCycles[kSplitVariants] = {185.0, 228.0, 272.0};
+static constexpr double kEdgeCycles = 50.0;
+static constexpr double kItemRowCycles = 400.0;
+
+// Weights whose parts would leave the normal range of bf16 stay on the fp32
+// items.
+static constexpr float kMinWeight = 0x1p-64f, kMaxWeight = 0x1p64f;
+
+static uint16_t bf16_rn(float x) {
+    uint32_t u;
+    std::memcpy(&u, &x, 4);
+    u += 0x7fffu + ((u >> 16) & 1u);
+    return (uint16_t)(u >> 16);
+}
+static float bf16_value(uint16_t b) {
+    const uint32_t u = (uint32_t)b << 16;
+    float x;
+    std::memcpy(&x, &u, 4);
+    return x;
+}
+// x = p[0] + p[1] + p[2] exactly (each remainder is exact in fp32)
+static void split3(float x, uint16_t p[3]) {
+    p[0] = bf16_rn(x);
+    const float r = x - bf16_value(p[0]);
+    p[1] = bf16_rn(r);
+    p[2] = bf16_rn(r - bf16_value(p[1]));
+}
+
+static int64_t outputs(const rocket_kernels *k, int32_t i, int64_t L) {
+    return L + 2 * (int64_t)k->padding[i] - (int64_t)(k->length[i] - 1) * k->dilation[i];
+}
+
+bool split_eligible(const rocket_kernels *k, int32_t L) {
+    if (k->n_channels > 1 || L <= kSeriesMaxL) return false;
+    for (int32_t i = 0; i < k->n_kernels; ++i) {
+        if (outputs(k, i, L) > kSplitMaxOutputs) return false;
+        for (int32_t j = 0; j < k->length[i]; ++j) {
+            const float w = std::fabs(k->weights[(int64_t)i * k->max_len + j]);
+            if (w != 0.0f && !(w >= kMinWeight && w <= kMaxWeight)) return false;
+        }
+    }
+    return true;
+}
+
+namespace {
+
+struct Row {
+    int32_t k;
+    int v;  // variant of its own length
+    int64_t O;
+};
+
+struct Group {
+    int variant = 0;
+    std::vector<int32_t> slot;    // kernel ids, at most kSplitRows
+    int64_t widths[4] = {};       // the different O of its kernels
+    int n_widths = 0;
+    int64_t n_cols = 0, o_min = 0;
+    double cost = 0.0;
+};
+
+void group_bounds(const Group &g, int32_t L, int32_t d, bool even, int32_t reach, int64_t *s0, int64_t *lo,
+                  int64_t *hi) {
+    const int frame = kSplitFrame[g.variant];
+    // lo + hi of every row's range of frame-tap-0 indices
+    *s0 = ((int64_t)L - (int64_t)(even ? frame - 2 : frame - 1) * d - g.n_cols) / 2;
+    const int64_t in_lo = (g.n_cols - g.o_min) / 2, in_hi = in_lo + g.o_min;
+    const int64_t first = std::max<int64_t>(in_lo, -(int64_t)kSplitMargin - *s0);
+    const int64_t last = std::min<int64_t>(in_hi - 1, (int64_t)L + kSplitMargin - 1 - *s0 - (int64_t)reach * d);
+    const int64_t n_blocks = (g.n_cols + kSplitBlock - 1) / kSplitBlock;
+    *lo = std::min(n_blocks, first <= 0 ? 0 : (first + kSplitBlock - 1) / kSplitBlock);
+    *hi = last < kSplitBlock - 1 ? 0 : (last + 1) / kSplitBlock;
+    if (*hi <= *lo) *lo = *hi = n_blocks;
+}
+
+// Cut rows (in the given order) into groups of at most 32 rows and as many
+// widths as the group's variant can mask.
+// (out null: only their cost).
+void cut(const Row *rows, size_t n, int32_t L, int32_t d, bool even, std::vector<Group> *out, double &cost) {
+    Group g;
+    size_t n_slots = 0;
+    auto flush = [&]() {
+        if (n_slots == 0) return;
+        int64_t s0, lo, hi;
+        group_bounds(g, L, d, even, kSplitFrame[g.variant] - 1, &s0, &lo, &hi);
+        const int64_t tiles = (g.n_cols + kSplitTile - 1) / kSplitTile;
+        const int64_t clean = 2 * (hi - lo);
+        g.cost = (double)tiles * kTileCycles[g.variant] + (double)(tiles - std::min(tiles, clean)) * kEdgeCycles +
+                 kItemRowCycles;
+        cost += g.cost;
+        if (out) out->push_back(std::move(g));
+        g = Group();
+        n_slots = 0;
+    };
+    for (size_t i = 0; i < n; ++i) {
+        const Row &r = rows[i];
+        auto known = [&]() {
+            for (int w = 0; w < g.n_widths; ++w)
+                if (g.widths[w] == r.O) return true;
+            return false;
+        };
+        const int v = std::max(g.variant, r.v);
+        if (n_slots == (size_t)kSplitRows || (!known() && g.n_widths == kSplitWidths[v])) flush();
+        if (n_slots == 0) g.n_cols = g.o_min = r.O;
+        if (!known()) g.widths[g.n_widths++] = r.O;
+        if (out) g.slot.push_back(r.k);
+        ++n_slots;
+        g.variant = std::max(g.variant, r.v);
+        g.n_cols = std::max(g.n_cols, r.O);
+        g.o_min = std::min(g.o_min, r.O);
+    }
+    flush();
+}
+
+// The same of a group's kernels as fp32 items: 4-kernel MFMA groups and VALU
+// items for the rest, per (length class, O).  kFp32Factor: measured time over
+// these issue cycles, relative to the split items' (1.3-1.5 times; passes are
+// 2.5 % faster with it and flat from 1.15 to 1.5).
+constexpr double kFp32Factor = 1.3;
+
+double fp32_cycles(const Group &g, const rocket_kernels *k, int64_t L) {
+    int n[kSplitVariants][4] = {};
+    for (int32_t i : g.slot)
+        ++n[ell_index_for(k->length[i])][std::find(g.widths, g.widths + g.n_widths, outputs(k, i, L)) - g.widths];
+    double c = 0.0;
+    for (int e = 0; e < kSplitVariants * 4; ++e) {
+        const int count = n[e / 4][e % 4];
+        const double ell = kEllValues[e / 4];
+        const double tiles = (double)((g.widths[e % 4] + kTile - 1) / kTile);
+        const int full = count / 4, rest = count % 4;
+        double t = full * (ell * 8.7 + 27.0);
+        if (rest == 3) t += ell * 8.7 + 27.0;
+        if (rest == 1 || rest == 2) t += rest * (ell * 4.5 + 6.75);
+        c += tiles * t + 25.0 * count;
+    }
+    return kFp32Factor * c;
+}
+
+}  // namespace
+
+// The kernels of one dilation and length parity, grouped in the cheapest of a
+// few ways: lengths apart or together (a short kernel in a longer frame), rows
+// of all widths together or apart.  Small dilations have many kernels of
+// nearly the same O and run best with lengths apart; at large ones an item is
+// filled only by everything the dilation has.
+static std::vector<Group> best_groups(const std::vector<Row> &rows, int32_t L, int32_t d, bool even) {
+    // which variants run together: {7}{9}{11}, {7,9,11}, {7}{9,11}, {7,9}{11}
+    static const int kParts[4][kSplitVariants] = {{0, 1, 2}, {0, 0, 0}, {0, 1, 1}, {0, 0, 1}};
+    // longest frame first, or widest first
+    std::vector<Row> order[2] = {rows, rows}, sel;
+    std::stable_sort(order[0].begin(), order[0].end(),
+                     [](const Row &a, const Row &b) { return a.v != b.v ? a.v > b.v : a.O > b.O; });
+    std::stable_sort(order[1].begin(), order[1].end(),
+                     [](const Row &a, const Row &b) { return a.O != b.O ? a.O > b.O : a.v > b.v; });
+    auto run = [&](int part, int how, std::vector<Group> *out) {
+        double cost = 0.0;
+        for (int q = 0; q < kSplitVariants; ++q) {
+            const Row *r = order[how == 0 ? 0 : 1].data();
+            size_t n = rows.size();
+            if (part != 1) {
+                sel.clear();
+                for (size_t i = 0; i < rows.size(); ++i)
+                    if (kParts[part][r[i].v] == q) sel.push_back(r[i]);
+                r = sel.data();
+                n = sel.size();
+            } else if (q > 0) {
+                break;
+            }
+            // how 2: a group boundary wherever O changes
+            for (size_t i = 0; i < n;) {
+                size_t j = how == 2 ? i : n;
+                while (j < n && r[j].O == r[i].O) ++j;
+                cut(r + i, j - i, L, d, even, out, cost);
+                i = j;
+            }
+        }
+        return cost;
+    };
+    int best_part = 1, best_how = 0;
+    // (a handful of kernels makes one group or none)
+    if (rows.size() > 6) {
+        double best = -1.0;
+        for (int part = 0; part < 4; ++part)
+            for (int how = 0; how < 3; ++how) {
+                const double c = run(part, how, nullptr);
+                if (best < 0.0 || c < best) {
+                    best = c;
+                    best_part = part;
+                    best_how = how;
+                }
+            }
+    }
+    std::vector<Group> out;
+    run(best_part, best_how, &out);
+    return out;
+}
+
+// The bf16 pair of (plane word, weight part) slots: word 0 = (x1, x2) and
+// word 1 = (x3, x1).
+static uint32_t pair16(uint32_t lo, uint32_t hi) { return lo | (hi << 16); }
+
+// The fragment whose dword 3 is the mask slot.
+static constexpr int kSplitMaskFrag[kSplitVariants] = {0, 2, 1};
+
+static void add_item(SplitPlan &P, const Group &g, const rocket_kernels *k, int32_t L, int32_t d, bool even) {
+    const int frame = kSplitFrame[g.variant], nf = kSplitFrags[g.variant];
+    SplitItem it;
+    std::memset(&it, 0, sizeof(it));
+    it.variant = g.variant;
+    it.d = d;
+    it.n_cols = (int32_t)g.n_cols;
+    it.a_off = (int32_t)(P.a.size() / 4);
+    it.r_off = (int32_t)P.kid.size();
+    // negated weights (the accumulators hold -y, see the kernel), split, by
+    // matrix row and frame tap
+    uint16_t w[kSplitRows][12][3] = {};
+    std::vector<float> cinit(kSplitRows, 0.0f);  // [half][reg]
+    std::array<int, kSplitRows> cls{};           // the row's width, by matrix row; -1 = empty
+    cls.fill(-1);
+    for (int i = 0; i < g.n_widths; ++i) it.width[i] = (int32_t)g.widths[i];
+    for (int q = 0; q < kSplitRows; ++q) {
+        const int32_t kk = q < (int)g.slot.size() ? g.slot[q] : -1;
+        P.kid.push_back(kk);
+        P.inv_O.push_back(kk >= 0 ? 1.0 / (double)outputs(k, kk, L) : 0.0);
+        if (kk < 0) continue;
+        const int len = k->length[kk], f = (frame - len) / 2;
+        for (int j = 0; j < len; ++j) {
+            uint16_t p[3];
+            split3(-k->weights[(int64_t)kk * k->max_len + j], p);
+            std::copy(p, p + 3, w[split_matrix_row(q)][f + j]);
+            it.reach = std::max(it.reach, f + j);
+        }
+        const float b = k->bias[kk];
+        cinit[(q & 1) * (kSplitRows / 2) + q / 2] = b == 0.0f ? 0.0f : -b;
+        cls[split_matrix_row(q)] = (int)(std::find(g.widths, g.widths + g.n_widths, outputs(k, kk, L)) - g.widths);
+    }
+    int64_t s0, lo, hi;
+    group_bounds(g, L, d, even, it.reach, &s0, &lo, &hi);
+    it.s0 = (int32_t)s0;
+    it.clean_lo = (int32_t)lo;
+    it.clean_hi = (int32_t)hi;
+    it.cost = (int32_t)std::min(g.cost, 1e9);
+    // fragments in the order of the kernel's MFMAs, dword i of lane (matrix
+    // row m, half h).  The main words' taps are 4 h + i; the tail is taps 8 up.
+    enum Kind { kZero, kW13, kW22, kW11, kMask };  // x3 w1 + x1 w3, (x1 + x2) w2, (x1 + x2) w1
+    P.a.resize(P.a.size() + (size_t)nf * kWave * 4);
+    uint32_t *dst = P.a.data() + P.a.size() - (size_t)nf * kWave * 4;
+    for (int fr = 0; fr < nf; ++fr)
+        for (int h = 0; h < 2; ++h)
+            for (int i = 0; i < 4; ++i) {
+                Kind kind = kZero;
+                int tap = 4 * h + i;
+                if (fr == kSplitMaskFrag[g.variant] && i == 3 && (g.variant > 0 || h == 1)) {
+                    kind = kMask;
+                } else if (fr == 0) {
+                    kind = kW13;
+                } else if (fr == nf - 1) {
+                    kind = kW11;
+                } else if (fr == (g.variant == 2 ? 2 : 1)) {
+                    kind = kW22;
+                } else if (g.variant == 1) {
+                    // tail: half 0 word 0 of tap 8 by w2, word 1; half 1 word 0 by w1
+                    if (i == 0) kind = h == 0 ? kW22 : kW11;
+                    if (i == 2 && h == 0) kind = kW13;
+                    tap = 8;
+                } else {
+                    // tail: taps 8 + i, half 0 word 0 (by w2, then w1), half 1 word 1
+                    if (fr == 1) kind = h == 0 ? kW22 : kW13;
+                    if (fr == 3 && h == 0) kind = kW11;
+                    tap = 8 + i;
+                }
+                const int c0 = g.variant > 0 ? 2 * h : 0;  // the mask slot's first width
+                for (int m = 0; m < kSplitRows; ++m) {
+                    const uint16_t *p = w[m][tap];
+                    uint32_t v = 0;
+                    if (kind == kW13) v = pair16(p[0], p[2]);
+                    if (kind == kW22) v = pair16(p[1], p[1]);
+                    if (kind == kW11) v = pair16(p[0], p[0]);
+                    if (kind == kMask)
+                        v = pair16(cls[m] == c0 ? kSplitMask : 0u, cls[m] == c0 + 1 ? kSplitMask : 0u);
+                    dst[((size_t)fr * kWave + 32 * h + m) * 4 + i] = v;
+                }
+            }
+    P.cinit.insert(P.cinit.end(), cinit.begin(), cinit.end());
+    P.items.push_back(it);
+    P.cost += g.cost;
+}
+
+// Kernels that fp32 items run faster are left to them only where that saves
+// this share of the pass (they stage the series again, in workgroups or a
+// launch of their own).
+static constexpr double kRestMinGain = 0.02;
+
+rocket_status build_split_plan(const rocket_kernels *k, int32_t L, SplitPlan *out) {
+    try {
+        SplitPlan P;
+        P.L = L;
+        std::map<std::pair<int32_t, bool>, std::vector<Row>> by_dil;
+        for (int32_t i = 0; i < k->n_kernels; ++i)
+            by_dil[{k->dilation[i], k->length[i] % 2 == 0}].push_back(
+                Row{i, ell_index_for(k->length[i]), outputs(k, i, L)});
+        // by their own numbers, so that a kernel's item, and with it the
+        // rounding of its dot products, does not depend on the set's order
+        auto before = [&](const Row &x, const Row &y) {
+            if (k->bias[x.k] != k->bias[y.k]) return k->bias[x.k] < k->bias[y.k];
+            const float *wx = k->weights + (int64_t)x.k * k->max_len, *wy = k->weights + (int64_t)y.k * k->max_len;
+            const int n = std::min(k->length[x.k], k->length[y.k]);
+            const auto d = std::mismatch(wx, wx + n, wy);
+            return d.first != wx + n ? *d.first < *d.second : x.k < y.k;
+        };
+        for (auto &e : by_dil) std::sort(e.second.begin(), e.second.end(), before);
+        struct Choice {
+            int32_t d;
+            bool even;
+            Group g;
+            double fp32;
+        };
+        std::vector<Choice> all;
+        double total = 0.0, gain = 0.0;
+        for (const auto &e : by_dil)
+            for (Group &g : best_groups(e.second, L, e.first.first, e.first.second)) {
+                const double c = fp32_cycles(g, k, L);
+                total += std::min(g.cost, c);
+                gain += std::max(0.0, g.cost - c);
+                all.push_back(Choice{e.first.first, e.first.second, std::move(g), c});
+            }
+        const bool leave = gain > kRestMinGain * total;
+        size_t words = 0;
+        for (const Choice &c : all) words += (size_t)kSplitFrags[c.g.variant] * kWave * 4;
+        P.a.reserve(words);
+        for (const Choice &c : all) {
+            if (leave && c.fp32 < c.g.cost) {
+                P.rest.insert(P.rest.end(), c.g.slot.begin(), c.g.slot.end());
+                P.rest_cost += c.fp32;
+            } else {
+                add_item(P, c.g, k, L, c.d, c.even);
+            }
+        }
+        std::sort(P.rest.begin(), P.rest.end());
+        std::vector<int32_t> variant, cost;
+        for (const SplitItem &it : P.items) {
+            variant.push_back(it.variant);
+            cost.push_back(it.cost);
+        }
+        order_items(variant, cost, kSplitVariants, P.order, P.split_begin, P.layout_off);
+        *out = std::move(P);
+        return ROCKET_OK;
+    } catch (const std::bad_alloc &) {
+        return ROCKET_ERR_OOM;
+    } catch (...) {
+        return ROCKET_ERR_INTERNAL;
+    }
+}
+
+}  // namespace rocket

@@ -159,6 +159,92 @@ rocket_status build_minirocket_plan(const rocket_minirocket_params *m, HostPlan 
 // split_begin, layout_off).
 void build_item_orders(HostPlan &P);
 
+// ---------------------------------------------------------------------------
+// Split items (univariate plans of series longer than kSeriesMaxL): the dot
+// products on v_mfma_f32_32x32x16_bf16, with every fp32 weight and series
+// value split into three bf16 parts (8 + 8 + 8 significant bits, so the three
+// parts hold all 24).  Of the nine part products the seven largest are summed
+// (dropped: x2 w3 and x3 w3, below 2^-26 of the product).  An item holds up to
+// 32 kernels of one dilation: the rows of the MFMA.  Its columns are 32
+// consecutive positions, its contraction index the taps and their parts.
+//
+// Kernels of any padding, and of shorter lengths, share an item: kernel k of
+// length len sits in a frame of `frame` taps (7, 9 or 11) at frame tap
+// f = (frame - len) / 2, and column c stands for the outputs whose frame tap 0
+// reads series index s0 + c.  The valid columns of every row are then centred
+// on the same point (series length minus frame span, halved), a row with O
+// outputs being valid where |2 c + 1 - n_cols| < O, with n_cols the largest O.
+// (Kernels of even and odd length have centres half a dilation apart and do
+// not share items.)
+//
+// LDS holds each staged row twice as 32-bit words, one per position: word 0 =
+// (x1, x2), word 1 = (x3, x1) (low half first), kSplitMargin zeros around.
+// ---------------------------------------------------------------------------
+constexpr int kSplitRows = 32;             // kernels per item
+constexpr int kSplitTile = 32;             // columns per MFMA
+constexpr int kSplitBlock = 64;            // columns per block: two tiles
+constexpr int kSplitMargin = kSplitBlock;  // zeros on each side of a staged row
+constexpr int kSplitVariants = 3;          // by frame: 7, 9, 11 taps
+constexpr int kSplitFrame[kSplitVariants] = {7, 9, 11};
+constexpr int kSplitFrags[kSplitVariants] = {3, 4, 5};  // MFMAs (A fragments) per tile
+constexpr int64_t kSplitMaxOutputs = 65535;  // counts are kept in 16-bit halves
+
+// Rows of an item have at most kSplitWidths[variant] different O.  Columns
+// outside a row's range are masked by the MFMA itself: each variant has a word
+// slot per lane half that no tap uses (the eighth tap of a 7-tap frame; the
+// tail's last word otherwise), whose weights are kSplitMask in the 16-bit half
+// of the row's width (halves: widths 0, 1 in lane half 0, 2, 3 in half 1; the
+// 7-tap frame has half 1 only, widths 0, 1).  Where the kernel puts kSplitMask
+// into that half of the word the product overflows to +infinity, elsewhere the
+// word is zero and adds nothing.
+constexpr int kSplitWidths[kSplitVariants] = {2, 4, 4};
+constexpr uint32_t kSplitMask = 0x7180u;  // 2^100 as bf16
+
+struct alignas(16) SplitItem {
+    int32_t variant;
+    int32_t d;         // dilation
+    int32_t s0;        // series index of frame tap 0 at column 0
+    int32_t n_cols;    // columns: the largest O of the item's kernels
+    int32_t clean_lo;  // blocks [clean_lo, clean_hi) need neither a mask nor a clamp:
+    int32_t clean_hi;  //   every row valid, every read within the margins
+    int32_t a_off;     // first A fragment, in 16-byte words: [frags][64 lanes]
+    int32_t r_off;     // first row entry (32 per item)
+    int32_t reach;     // last frame tap that holds a weight
+    int32_t cost;      // issue cycles per series (scheduling weight)
+    int32_t width[4];  // the O that a mask half stands for
+    int32_t unused[2];
+};
+static_assert(sizeof(SplitItem) == 64, "SplitItem must stay 64 bytes");
+
+// The result register i (0..15) and lane half h (0, 1) of v_mfma_f32_32x32
+// hold matrix row 8 (i / 4) + 4 h + i % 4; rows are numbered q = 2 i + h here.
+constexpr int split_matrix_row(int q) { return 8 * (q / 8) + 4 * (q & 1) + (q / 2) % 4; }
+
+struct SplitPlan {
+    int32_t L = 0;
+    std::vector<SplitItem> items;
+    std::vector<uint32_t> a;      // A fragments, bf16 pairs: [item][frag][lane][4]
+    std::vector<float> cinit;     // per item [half][reg]: -bias
+    std::vector<int32_t> kid;     // per item [row q]: kernel id, -1 = empty
+    std::vector<double> inv_O;    // per item [row q]
+    std::vector<int32_t> order;   // as HostPlan
+    std::vector<int32_t> split_begin;
+    std::vector<int32_t> layout_off;
+    std::vector<int32_t> rest;    // kernels left to the fp32 items (ascending)
+    double cost = 0.0;            // issue cycles per series of the items
+    double rest_cost = 0.0;       // and of the rest as fp32 items
+};
+
+// Whether a kernel set can run as split items on series of length L.
+bool split_eligible(const rocket_kernels *k, int32_t L);
+// Groups the kernels into split items; those that fp32 items run faster are
+// left in `rest` when together they carry a real share of the work.
+rocket_status build_split_plan(const rocket_kernels *k, int32_t L, SplitPlan *out);
+
+// Item orders of items given by variant and cost (see build_item_orders).
+void order_items(const std::vector<int32_t> &variant, const std::vector<int32_t> &cost, int n_variants,
+                 std::vector<int32_t> &order, std::vector<int32_t> &split_begin, std::vector<int32_t> &layout_off);
+
 // Element `index` of the SplitMix64 sequence started at `seed`.
 uint64_t splitmix64_at(uint64_t seed, uint64_t index);
 

@@ -1,0 +1,136 @@
+"""Split items (fp32 dot products as bf16 part products, series longer than
+128 samples) where they can go wrong: the shortest and longest rows they take,
+lengths that leave one column in the last tile or block, 1 to 33 kernels of a
+dilation, every kernel length with paddings that are not centred, rows of many
+widths in one item, series scaled to the ends of the fp32 range, and rows
+beside a row of NaN and infinities."""
+import sys
+
+import numpy as np
+import pytest
+
+from _util import assert_mpv_parity, assert_parity, kernel_set
+
+pytestmark = pytest.mark.gpu
+
+
+def _log(msg):
+    print("[gpu-split] " + msg, flush=True)
+    sys.stdout.flush()
+
+
+@pytest.fixture(scope="module")
+def env():
+    import torch
+
+    import paper_2601_17091_amd as rk
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    rk.library()
+    return torch, rk
+
+
+def _run(env, ks, X, **kw):
+    torch, rk = env
+    F = rk.Plan(ks, X.shape[1], **kw).transform(torch.from_numpy(X).cuda())
+    torch.cuda.synchronize()
+    return F.cpu().numpy()
+
+
+def _check(F, ref, mpv, what):
+    (assert_mpv_parity if mpv else assert_parity)(F, ref, what)
+
+
+# 129: the shortest; 193, 257: one column in a last tile, a last block; 1,021:
+# odd; 3,200: the last with two rows per workgroup; 6,463 / 6,464 / 6,465 and
+# 9,983 / 9,984 / 9,985: around the rows that take the next workgroup shape;
+# 20,255: near the longest; 20,300: too long (fp32 items)
+@pytest.mark.parametrize("L", [129, 193, 257, 1021, 3200, 6463, 6464, 6465, 9983, 9984, 9985, 20255, 20300])
+def test_row_lengths(env, oracle, L):
+    _, rk = env
+    K = 400 if L < 4000 else 120
+    ks = rk.generate_kernels(3000 + L, K, L)
+    rng = np.random.default_rng(L)
+    X = rng.standard_normal((5 if L < 4000 else 2, L)).cumsum(1)
+    X = ((X - X.mean(1, keepdims=True)) / X.std(1, keepdims=True)).astype(np.float32)
+    ref = oracle.transform(X, ks)
+    for mpv in (False, True):
+        _log("L=%d mpv=%s" % (L, mpv))
+        _check(_run(env, ks, X, mpv=mpv), ref, mpv, "L=%d" % L)
+
+
+@pytest.mark.parametrize("clamped", [False, True])
+@pytest.mark.parametrize("L", [131, 320])
+def test_lengths_and_paddings(env, oracle, L, clamped):
+    """Every length from 1 to 11 with paddings 0 .. 40, so that one dilation
+    holds rows of many widths (an item masks two or four) and of both length
+    parities; dilations up to O = 1."""
+    rng = np.random.default_rng(17 + L)
+    ln, dil, pad, w = [], [], [], []
+    for d in (1, 2, 3, 12, 13, 26):
+        for length in range(1, 12):
+            for p in rng.integers(0, 41, 1 + (d * length) % 5):
+                if L + 2 * p - (length - 1) * d < 1:
+                    p = ((length - 1) * d) // 2
+                ln.append(length)
+                dil.append(d)
+                pad.append(int(p))
+                w.append(rng.standard_normal(length))
+    for length, d in ((11, (L - 1) // 10), (9, (L - 1) // 8), (7, (L - 1) // 6)):
+        ln += [length] * 3
+        dil += [d] * 3
+        pad += [0] * 3
+        w += [rng.standard_normal(length) for _ in range(3)]
+    ks = kernel_set(ln, dil, pad, rng.uniform(-1, 1, len(ln)), w)
+    X = rng.standard_normal((4, L)).astype(np.float32)
+    _log("lengths and paddings L=%d clamped=%s, %d kernels" % (L, clamped, len(ln)))
+    ref = oracle.transform(X, ks)
+    for mpv in (False, True):
+        _check(_run(env, ks, X, mpv=mpv, clamped=clamped), ref, mpv, "paddings")
+
+
+@pytest.mark.parametrize("count", [1, 2, 15, 31, 32, 33, 65])
+def test_kernels_per_dilation(env, oracle, count):
+    """A dilation's kernels fill one item, one less, one more, and two."""
+    rng = np.random.default_rng(count)
+    L = 400
+    ln = [7, 9, 11] * count
+    dil = [2] * (3 * count)
+    pad = [(l - 1) if rng.integers(2) else 0 for l in ln]
+    ks = kernel_set(ln, dil, pad, rng.uniform(-1, 1, len(ln)), [rng.standard_normal(l) for l in ln])
+    X = rng.standard_normal((3, L)).astype(np.float32)
+    _log("%d kernels of each length at one dilation" % count)
+    _check(_run(env, ks, X), oracle.transform(X, ks), False, "count=%d" % count)
+
+
+@pytest.mark.parametrize("e", [-80, -40, 40, 110])
+def test_power_of_two_scaling(env, e):
+    """Scaling the series and the biases by 2^e scales every part, product
+    and sum exactly (all parts stay normal at 2^-80): PPV is unchanged and
+    MAX scales bit for bit, up to sums near the fp32 maximum."""
+    _, rk = env
+    ks = rk.generate_kernels(77, 500, 300)
+    rng = np.random.default_rng(5)
+    X = rng.standard_normal((3, 300)).astype(np.float32)
+    a = _run(env, ks, X)
+    ks2 = dict(ks, bias=np.ldexp(ks["bias"], e).astype(np.float32))
+    _log("scaled by 2^%d" % e)
+    b = _run(env, ks2, np.ldexp(X, e).astype(np.float32))
+    np.testing.assert_array_equal(a[:, 0::2], b[:, 0::2])
+    np.testing.assert_array_equal(np.ldexp(a[:, 1::2].astype(np.float64), e), b[:, 1::2].astype(np.float64))
+
+
+def test_neighbour_rows_do_not_mix(env):
+    """Rows of NaN and of infinities leave the features of the rows staged
+    beside them as they are alone."""
+    torch, rk = env
+    for L in (150, 500):
+        ks = rk.generate_kernels(78, 600, L)
+        rng = np.random.default_rng(6)
+        X = rng.standard_normal((7, L)).astype(np.float32)
+        want = _run(env, ks, X)
+        Y = X.copy()
+        Y[1], Y[4], Y[6] = np.nan, np.inf, -np.inf
+        _log("rows of NaN and infinity, L=%d" % L)
+        got = _run(env, ks, Y)
+        keep = [0, 2, 3, 5]
+        np.testing.assert_array_equal(got[keep], want[keep])
