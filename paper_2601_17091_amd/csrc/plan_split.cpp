@@ -25,6 +25,7 @@ namespace rocket {
 static constexpr double kTileCycles[kSplitVariants] = {185.0, 228.0, 272.0};
 static constexpr double kEdgeCycles = 50.0;
 static constexpr double kItemRowCycles = 400.0;
+static constexpr double kSeriesRowCycles = 1000.0;  // series-lane: an item's stores per 32 series
 
 // Weights whose parts would leave the normal range of bf16 stay on the fp32
 // items.
@@ -55,7 +56,7 @@ static int64_t outputs(const rocket_kernels *k, int32_t i, int64_t L) {
 }
 
 bool split_eligible(const rocket_kernels *k, int32_t L) {
-    if (k->n_channels > 1 || L <= kSeriesMaxL) return false;
+    if (k->n_channels > 1) return false;
     for (int32_t i = 0; i < k->n_kernels; ++i) {
         if (outputs(k, i, L) > kSplitMaxOutputs) return false;
         for (int32_t j = 0; j < k->length[i]; ++j) {
@@ -83,17 +84,19 @@ struct Group {
     double cost = 0.0;
 };
 
-void group_bounds(const Group &g, int32_t L, int32_t d, bool even, int32_t reach, int64_t *s0, int64_t *lo,
-                  int64_t *hi) {
+// The blocks of `block` columns whose rows are all valid and whose reads stay
+// within `margin` zeros around the series.
+void group_bounds(const Group &g, int32_t L, int32_t d, bool even, int32_t reach, int margin, int block, int64_t *s0,
+                  int64_t *lo, int64_t *hi) {
     const int frame = kSplitFrame[g.variant];
     // lo + hi of every row's range of frame-tap-0 indices
     *s0 = ((int64_t)L - (int64_t)(even ? frame - 2 : frame - 1) * d - g.n_cols) / 2;
     const int64_t in_lo = (g.n_cols - g.o_min) / 2, in_hi = in_lo + g.o_min;
-    const int64_t first = std::max<int64_t>(in_lo, -(int64_t)kSplitMargin - *s0);
-    const int64_t last = std::min<int64_t>(in_hi - 1, (int64_t)L + kSplitMargin - 1 - *s0 - (int64_t)reach * d);
-    const int64_t n_blocks = (g.n_cols + kSplitBlock - 1) / kSplitBlock;
-    *lo = std::min(n_blocks, first <= 0 ? 0 : (first + kSplitBlock - 1) / kSplitBlock);
-    *hi = last < kSplitBlock - 1 ? 0 : (last + 1) / kSplitBlock;
+    const int64_t first = std::max<int64_t>(in_lo, -(int64_t)margin - *s0);
+    const int64_t last = std::min<int64_t>(in_hi - 1, (int64_t)L + margin - 1 - *s0 - (int64_t)reach * d);
+    const int64_t n_blocks = (g.n_cols + block - 1) / block;
+    *lo = std::min(n_blocks, first <= 0 ? 0 : (first + block - 1) / block);
+    *hi = last < block - 1 ? 0 : (last + 1) / block;
     if (*hi <= *lo) *lo = *hi = n_blocks;
 }
 
@@ -106,11 +109,18 @@ void cut(const Row *rows, size_t n, int32_t L, int32_t d, bool even, std::vector
     auto flush = [&]() {
         if (n_slots == 0) return;
         int64_t s0, lo, hi;
-        group_bounds(g, L, d, even, kSplitFrame[g.variant] - 1, &s0, &lo, &hi);
-        const int64_t tiles = (g.n_cols + kSplitTile - 1) / kSplitTile;
-        const int64_t clean = 2 * (hi - lo);
-        g.cost = (double)tiles * kTileCycles[g.variant] + (double)(tiles - std::min(tiles, clean)) * kEdgeCycles +
-                 kItemRowCycles;
+        if (L <= kSeriesMaxL) {
+            // series-lane: a tile is one position of 32 series
+            group_bounds(g, L, d, even, kSplitFrame[g.variant] - 1, kSplitSeriesMargin, 2, &s0, &lo, &hi);
+            g.cost = ((double)g.n_cols * kTileCycles[g.variant] + (double)(g.n_cols - 2 * (hi - lo)) * kEdgeCycles +
+                      kSeriesRowCycles) / kSplitTile;
+        } else {
+            group_bounds(g, L, d, even, kSplitFrame[g.variant] - 1, kSplitMargin, kSplitBlock, &s0, &lo, &hi);
+            const int64_t tiles = (g.n_cols + kSplitTile - 1) / kSplitTile;
+            const int64_t clean = 2 * (hi - lo);
+            g.cost = (double)tiles * kTileCycles[g.variant] + (double)(tiles - std::min(tiles, clean)) * kEdgeCycles +
+                     kItemRowCycles;
+        }
         cost += g.cost;
         if (out) out->push_back(std::move(g));
         g = Group();
@@ -150,8 +160,13 @@ double fp32_cycles(const Group &g, const rocket_kernels *k, int64_t L) {
     for (int e = 0; e < kSplitVariants * 4; ++e) {
         const int count = n[e / 4][e % 4];
         const double ell = kEllValues[e / 4];
-        const double tiles = (double)((g.widths[e % 4] + kTile - 1) / kTile);
         const int full = count / 4, rest = count % 4;
+        if (L <= kSeriesMaxL) {
+            // series-lane MFMA items: 2 vector instructions to fold a register
+            c += (double)((count + 3) / 4 * g.widths[e % 4]) / kTile * (ell * 8.7 + 36.0);
+            continue;
+        }
+        const double tiles = (double)((g.widths[e % 4] + kTile - 1) / kTile);
         double t = full * (ell * 8.7 + 27.0);
         if (rest == 3) t += ell * 8.7 + 27.0;
         if (rest == 1 || rest == 2) t += rest * (ell * 4.5 + 6.75);
@@ -233,6 +248,7 @@ static void add_item(SplitPlan &P, const Group &g, const rocket_kernels *k, int3
     it.variant = g.variant;
     it.d = d;
     it.n_cols = (int32_t)g.n_cols;
+    it.n_rows = (int32_t)g.slot.size();
     it.a_off = (int32_t)(P.a.size() / 4);
     it.r_off = (int32_t)P.kid.size();
     // negated weights (the accumulators hold -y, see the kernel), split, by
@@ -242,10 +258,14 @@ static void add_item(SplitPlan &P, const Group &g, const rocket_kernels *k, int3
     std::array<int, kSplitRows> cls{};           // the row's width, by matrix row; -1 = empty
     cls.fill(-1);
     for (int i = 0; i < g.n_widths; ++i) it.width[i] = (int32_t)g.widths[i];
+    std::vector<float> div_O(2 * kSplitRows);
     for (int q = 0; q < kSplitRows; ++q) {
         const int32_t kk = q < (int)g.slot.size() ? g.slot[q] : -1;
         P.kid.push_back(kk);
-        P.inv_O.push_back(kk >= 0 ? 1.0 / (double)outputs(k, kk, L) : 0.0);
+        const int64_t O = kk >= 0 ? outputs(k, kk, L) : 1;
+        P.inv_O.push_back(1.0 / (double)O);
+        div_O[(q & 1) * kSplitRows + q / 2 * 2] = (float)O;
+        div_O[(q & 1) * kSplitRows + q / 2 * 2 + 1] = 1.0f / (float)O;
         if (kk < 0) continue;
         const int len = k->length[kk], f = (frame - len) / 2;
         for (int j = 0; j < len; ++j) {
@@ -259,10 +279,13 @@ static void add_item(SplitPlan &P, const Group &g, const rocket_kernels *k, int3
         cls[split_matrix_row(q)] = (int)(std::find(g.widths, g.widths + g.n_widths, outputs(k, kk, L)) - g.widths);
     }
     int64_t s0, lo, hi;
-    group_bounds(g, L, d, even, it.reach, &s0, &lo, &hi);
+    group_bounds(g, L, d, even, it.reach, kSplitMargin, kSplitBlock, &s0, &lo, &hi);
     it.s0 = (int32_t)s0;
     it.clean_lo = (int32_t)lo;
     it.clean_hi = (int32_t)hi;
+    group_bounds(g, L, d, even, it.reach, kSplitSeriesMargin, 2, &s0, &lo, &hi);
+    it.series_lo = (int32_t)lo;
+    it.series_hi = (int32_t)hi;
     it.cost = (int32_t)std::min(g.cost, 1e9);
     // fragments in the order of the kernel's MFMAs, dword i of lane (matrix
     // row m, half h).  The main words' taps are 4 h + i; the tail is taps 8 up.
@@ -306,6 +329,7 @@ static void add_item(SplitPlan &P, const Group &g, const rocket_kernels *k, int3
                 }
             }
     P.cinit.insert(P.cinit.end(), cinit.begin(), cinit.end());
+    P.div_O.insert(P.div_O.end(), div_O.begin(), div_O.end());
     P.items.push_back(it);
     P.cost += g.cost;
 }
@@ -314,6 +338,7 @@ static void add_item(SplitPlan &P, const Group &g, const rocket_kernels *k, int3
 // this share of the pass (they stage the series again, in workgroups or a
 // launch of their own).
 static constexpr double kRestMinGain = 0.02;
+static constexpr double kShortGain = 0.85;  // short series take split items below this share of the fp32 items' cost
 
 rocket_status build_split_plan(const rocket_kernels *k, int32_t L, SplitPlan *out) {
     try {
@@ -348,7 +373,17 @@ rocket_status build_split_plan(const rocket_kernels *k, int32_t L, SplitPlan *ou
                 gain += std::max(0.0, g.cost - c);
                 all.push_back(Choice{e.first.first, e.first.second, std::move(g), c});
             }
-        const bool leave = gain > kRestMinGain * total;
+        // short series: all kernels or none (the series-lane layout runs one
+        // kind of item), by the total
+        if (L <= kSeriesMaxL) {
+            double split = 0.0, fp32 = 0.0;
+            for (const Choice &c : all) {
+                split += c.g.cost;
+                fp32 += c.fp32;
+            }
+            if (split > kShortGain * fp32) all.clear();
+        }
+        const bool leave = L > kSeriesMaxL && gain > kRestMinGain * total;
         size_t words = 0;
         for (const Choice &c : all) words += (size_t)kSplitFrags[c.g.variant] * kWave * 4;
         P.a.reserve(words);

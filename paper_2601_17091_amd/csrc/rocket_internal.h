@@ -184,6 +184,7 @@ constexpr int kSplitRows = 32;             // kernels per item
 constexpr int kSplitTile = 32;             // columns per MFMA
 constexpr int kSplitBlock = 64;            // columns per block: two tiles
 constexpr int kSplitMargin = kSplitBlock;  // zeros on each side of a staged row
+constexpr int kSplitSeriesMargin = 8;      // series-lane layout: zero positions on each side
 constexpr int kSplitVariants = 3;          // by frame: 7, 9, 11 taps
 constexpr int kSplitFrame[kSplitVariants] = {7, 9, 11};
 constexpr int kSplitFrags[kSplitVariants] = {3, 4, 5};  // MFMAs (A fragments) per tile
@@ -211,10 +212,12 @@ struct alignas(16) SplitItem {
     int32_t r_off;     // first row entry (32 per item)
     int32_t reach;     // last frame tap that holds a weight
     int32_t cost;      // issue cycles per series (scheduling weight)
+    int32_t n_rows;    // kernels
     int32_t width[4];  // the O that a mask half stands for
-    int32_t unused[2];
+    int32_t series_lo; // as clean_lo and clean_hi, in blocks of two positions of the
+    int32_t series_hi; //   series-lane layout (kSplitSeriesMargin zero positions)
 };
-static_assert(sizeof(SplitItem) == 64, "SplitItem must stay 64 bytes");
+static_assert(sizeof(SplitItem) == 80, "SplitItem is 16-byte words");
 
 // The result register i (0..15) and lane half h (0, 1) of v_mfma_f32_32x32
 // hold matrix row 8 (i / 4) + 4 h + i % 4; rows are numbered q = 2 i + h here.
@@ -227,6 +230,7 @@ struct SplitPlan {
     std::vector<float> cinit;     // per item [half][reg]: -bias
     std::vector<int32_t> kid;     // per item [row q]: kernel id, -1 = empty
     std::vector<double> inv_O;    // per item [row q]
+    std::vector<float> div_O;     // per item [half][reg]: O and 1 / O as floats (series-lane layout)
     std::vector<int32_t> order;   // as HostPlan
     std::vector<int32_t> split_begin;
     std::vector<int32_t> layout_off;

@@ -66,6 +66,7 @@ struct SplitArgs {
     const float *cinit;
     const int32_t *kid;
     const double *inv_O;
+    const float *div_O;
     const int32_t *order;
     const int32_t *split_begin;
     int32_t nsplit, n_variants;
@@ -76,6 +77,9 @@ struct SplitArgs {
     int32_t pitch;        // words between staged rows: L + kMargin
     int32_t plane_words;  // words per plane
     int32_t vec4;         // rows are read 4 floats at a time (L a multiple of 4, X 16-byte aligned)
+    float *S;             // series-lane layout: features in slot order, s_rows series per slot column
+    int64_t s_rows;
+    int64_t s_floats;     // floats of S (bounds of checked builds)
 };
 
 struct CheckBounds {
@@ -136,15 +140,15 @@ __device__ __forceinline__ v16f mfma(const v4u &a, const v4u &b, const v16f &c) 
 // One block of NT tiles, FIRST blocks after the one the addresses stand for:
 // the words, the MFMAs (small parts first) and the fold.  plane: bytes from
 // plane 0 to plane 1; mask(u): the mask word of tile u (EDGE blocks; others
-// have zeros in its slot).
-template <int V, int NT, bool MPV, bool EDGE, int FIRST, typename Mask>
+// have zeros in its slot).  STRIDE: bytes from one tile's words to the next's.
+template <int V, int NT, bool MPV, bool EDGE, int FIRST, int STRIDE, typename Mask>
 __device__ __forceinline__ void block(const Addr<V> &ad, uint32_t plane, const v4u (&fa)[rocket::kSplitFrags[V]],
                                       const v16f &cinit, const Mask &mask, int h, Acc<MPV> &ac,
                                       const CheckBounds &cb) {
     v16f z[NT];
 #pragma unroll
     for (int u = 0; u < NT; ++u) {
-        const uint32_t off = 4u * (rocket::kSplitBlock * FIRST + rocket::kSplitTile * u);
+        const uint32_t off = (uint32_t)STRIDE * (2u * FIRST + u);
         v4u b0, b1, bt = {0u, 0u, 0u, 0u};
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -245,27 +249,34 @@ __device__ __forceinline__ uint32_t tree(uint32_t (&v)[N], int lane) {
     return dpp<Op, kDppQuadSwap1>(v[0]);
 }
 
+// An item's A fragments and start values.
+template <int V>
+__device__ __forceinline__ void load_fragments(const SplitItem &it, const SplitArgs &a, int lane,
+                                               v4u (&fa)[rocket::kSplitFrags[V]], v16f &cinit) {
+#pragma unroll
+    for (int f = 0; f < rocket::kSplitFrags[V]; ++f)
+        fa[f] = reinterpret_cast<const v4u *>(a.a)[it.a_off + f * rocket::kWave + lane];
+    const float4 *c4 = reinterpret_cast<const float4 *>(a.cinit + it.r_off + (lane >> 5) * kRegs);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const float4 c = c4[i];
+        cinit[4 * i] = c.x;
+        cinit[4 * i + 1] = c.y;
+        cinit[4 * i + 2] = c.z;
+        cinit[4 * i + 3] = c.w;
+    }
+}
+
+constexpr int kTileBytes = 4 * rocket::kSplitTile;
+
 // One item over the staged series.
 template <int V, bool MPV>
 __device__ __forceinline__ void run_split_item(const SplitItem &it, const SplitArgs &a, uint32_t lds0, uint32_t plane,
                                          int nrows, float *F0, int lane, const CheckBounds &cb) {
-    constexpr int NF = rocket::kSplitFrags[V];
     const int n = lane & 31, h = lane >> 5;
-    v4u fa[NF];
-#pragma unroll
-    for (int f = 0; f < NF; ++f) fa[f] = reinterpret_cast<const v4u *>(a.a)[it.a_off + f * rocket::kWave + lane];
+    v4u fa[rocket::kSplitFrags[V]];
     v16f cinit;
-    {
-        const float4 *c4 = reinterpret_cast<const float4 *>(a.cinit + it.r_off + h * kRegs);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const float4 c = c4[i];
-            cinit[4 * i] = c.x;
-            cinit[4 * i + 1] = c.y;
-            cinit[4 * i + 2] = c.z;
-            cinit[4 * i + 3] = c.w;
-        }
-    }
+    load_fragments<V>(it, a, lane, fa, cinit);
     // the row this lane writes after the reductions (even lanes): register
     // bits 3..0 = lane bits 4..1
     const int reg = (((lane >> 4) & 1) << 3) | (((lane >> 3) & 1) << 2) | (((lane >> 2) & 1) << 1) | ((lane >> 1) & 1);
@@ -316,9 +327,9 @@ __device__ __forceinline__ void run_split_item(const SplitItem &it, const SplitA
                 return (dist < wa ? 0u : rocket::kSplitMask) | (dist < wb ? 0u : rocket::kSplitMask << 16);
             };
             if (it.n_cols - c0 > rocket::kSplitTile)
-                block<V, 2, MPV, true, 0>(ad, plane, fa, cinit, mask, h, ac, cb);
+                block<V, 2, MPV, true, 0, kTileBytes>(ad, plane, fa, cinit, mask, h, ac, cb);
             else
-                block<V, 1, MPV, true, 0>(ad, plane, fa, cinit, mask, h, ac, cb);
+                block<V, 1, MPV, true, 0, kTileBytes>(ad, plane, fa, cinit, mask, h, ac, cb);
         };
         for (int b = 0; b < it.clean_lo; ++b) edge(b);
         Addr<V> ad;
@@ -337,14 +348,14 @@ __device__ __forceinline__ void run_split_item(const SplitItem &it, const SplitA
         // kUnroll blocks per address update (one with MPV, whose registers are
         // short: two measured 3.6 % slower)
         for (int b = 0; b + kUnroll <= n_clean; b += kUnroll) {
-            block<V, 2, MPV, false, 0>(ad, plane, fa, cinit, none, h, ac, cb);
-            if constexpr (kUnroll == 2) block<V, 2, MPV, false, 1>(ad, plane, fa, cinit, none, h, ac, cb);
+            block<V, 2, MPV, false, 0, kTileBytes>(ad, plane, fa, cinit, none, h, ac, cb);
+            if constexpr (kUnroll == 2) block<V, 2, MPV, false, 1, kTileBytes>(ad, plane, fa, cinit, none, h, ac, cb);
 #pragma unroll
             for (int i = 0; i < 4; ++i) ad.main[i] += i == 3 ? step3 : step;
 #pragma unroll
             for (int i = 0; i < tail_addrs(V); ++i) ad.tail[i] += step;
         }
-        if (n_clean % kUnroll) block<V, 2, MPV, false, 0>(ad, plane, fa, cinit, none, h, ac, cb);
+        if (n_clean % kUnroll) block<V, 2, MPV, false, 0, kTileBytes>(ad, plane, fa, cinit, none, h, ac, cb);
         for (int b = it.clean_hi; b < n_blocks; ++b) edge(b);
 
         // reductions over the 32 columns, then one store per row
@@ -401,8 +412,11 @@ __device__ __forceinline__ SplitItem load_split_item(ConstPtr<SplitItem> p) {
     it.r_off = p->r_off;
     it.reach = p->reach;
     it.cost = p->cost;
+    it.n_rows = p->n_rows;
 #pragma unroll
     for (int i = 0; i < 4; ++i) it.width[i] = p->width[i];
+    it.series_lo = p->series_lo;
+    it.series_hi = p->series_hi;
     return it;
 }
 
@@ -509,6 +523,197 @@ __global__ __launch_bounds__(BLOCK, MPV ? 2 : 3) void rocket_split_kernel(SplitA
     }
 }
 
+// ---------------------------------------------------------------------------
+// Series-lane layout (series of at most kSeriesMaxL samples, calls of many).
+// LDS holds 64 series position-major, 64 consecutive words per position and
+// plane: the 32 columns of a tile are 32 series at one position, a block is two
+// positions, and every lane keeps the counts and minima of its own series, so
+// nothing is reduced across lanes.  The same MFMAs in the same order as the
+// tiled layout, so PPV and MAX are bit for bit the same.  The features go to a
+// slot-ordered buffer, which rocket_slot_permute_kernel turns into F rows.
+// ---------------------------------------------------------------------------
+constexpr int kPosBytes = 4 * rocket::kWave;  // one position of a plane
+constexpr int kSM = rocket::kSplitSeriesMargin;
+
+template <int V, bool MPV>
+__device__ __forceinline__ void run_series_item(const SplitItem &it, const SplitArgs &a, uint32_t lds0, uint32_t plane,
+                                                int64_t series0, int n_series, int lane, const CheckBounds &cb) {
+    const int n = lane & 31, h = lane >> 5;
+    v4u fa[rocket::kSplitFrags[V]];
+    v16f cinit;
+    load_fragments<V>(it, a, lane, fa, cinit);
+    const int n_blocks = (it.n_cols + 1) / 2;
+    const bool idle = V == 0 && h == 1;
+    const int wa = (V > 0 && h) ? it.width[2] : it.width[0], wb = (V > 0 && h) ? it.width[3] : it.width[1];
+    constexpr int kUnroll = MPV ? 1 : 2;
+    constexpr uint32_t step = kUnroll * 2 * kPosBytes;
+    const uint32_t step3 = idle ? 0u : step;
+    for (int s0 = 0; s0 < n_series; s0 += rocket::kSplitTile) {
+        const int base = (int)lds0 + kSM * kPosBytes + 4 * (s0 + n);  // position 0
+        const uint32_t zero = (uint32_t)(base - kSM * kPosBytes);
+        int main0[4], tail0[3];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) main0[i] = base + kPosBytes * (it.s0 + min(4 * h + i, it.reach) * it.d);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) tail0[i] = base + kPosBytes * (it.s0 + min(8 + i, it.reach) * it.d);
+        const uint32_t tail_plane = V == 2 ? (uint32_t)h * plane : 0u;
+        Acc<MPV> ac;
+#pragma unroll
+        for (int i = 0; i < kRegs; ++i) {
+            ac.mn[i] = INFINITY;
+            if (MPV) ac.ps[i] = 0.0f;
+        }
+#pragma unroll
+        for (int j = 0; j < kRegs / 2; ++j) ac.cnt[j] = 0u;
+        const int lo = base - kSM * kPosBytes, hi = base + a.L * kPosBytes;
+        auto edge = [&](int b) {
+            const int c0 = 2 * b;
+            auto clamped = [&](int m) { return (uint32_t)min(max(m + c0 * kPosBytes, lo), hi); };
+            Addr<V> ad;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) ad.main[i] = clamped(main0[i]);
+            if (idle) ad.main[3] = zero;
+#pragma unroll
+            for (int i = 0; i < tail_addrs(V); ++i) ad.tail[i] = clamped(tail0[i]) + tail_plane;
+            auto mask = [&](int u) {
+                const int off = 2 * (c0 + u) + 1 - it.n_cols;
+                const int dist = max(off, -off);
+                return (dist < wa ? 0u : rocket::kSplitMask) | (dist < wb ? 0u : rocket::kSplitMask << 16);
+            };
+            if (it.n_cols - c0 > 1)
+                block<V, 2, MPV, true, 0, kPosBytes>(ad, plane, fa, cinit, mask, h, ac, cb);
+            else
+                block<V, 1, MPV, true, 0, kPosBytes>(ad, plane, fa, cinit, mask, h, ac, cb);
+        };
+        for (int b = 0; b < it.series_lo; ++b) edge(b);
+        Addr<V> ad;
+        const uint32_t start = (uint32_t)it.series_lo * 2 * kPosBytes;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) ad.main[i] = (uint32_t)main0[i] + start;
+        if (idle) ad.main[3] = zero;
+#pragma unroll
+        for (int i = 0; i < tail_addrs(V); ++i) ad.tail[i] = (uint32_t)tail0[i] + start + tail_plane;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(ad.main[i]));
+#pragma unroll
+        for (int i = 0; i < tail_addrs(V); ++i) asm volatile("" : "+v"(ad.tail[i]));
+        auto none = [](int) { return 0u; };
+        const int n_clean = it.series_hi - it.series_lo;
+        for (int b = 0; b + kUnroll <= n_clean; b += kUnroll) {
+            block<V, 2, MPV, false, 0, kPosBytes>(ad, plane, fa, cinit, none, h, ac, cb);
+            if constexpr (kUnroll == 2) block<V, 2, MPV, false, 1, kPosBytes>(ad, plane, fa, cinit, none, h, ac, cb);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) ad.main[i] += i == 3 ? step3 : step;
+#pragma unroll
+            for (int i = 0; i < tail_addrs(V); ++i) ad.tail[i] += step;
+        }
+        if (n_clean % kUnroll) block<V, 2, MPV, false, 0, kPosBytes>(ad, plane, fa, cinit, none, h, ac, cb);
+        for (int b = it.series_hi; b < n_blocks; ++b) edge(b);
+
+        // the features of the lane's series, rows 2 i + h
+        const float2 *div = reinterpret_cast<const float2 *>(a.div_O) + it.r_off + h * kRegs;
+        const bool mine = s0 + n < n_series;
+        float *out = a.S + ((int64_t)(it.r_off + h) * a.s_rows + series0 + s0 + n) * (MPV ? 3 : 2);
+#pragma unroll
+        for (int i = 0; i < kRegs; ++i) {
+            const uint32_t packed = ac.cnt[i / 2];  // see run_split_item
+            const uint32_t lo16 = (0u - packed) & 0xffffu;
+            const uint32_t c = (i & 1) ? (lo16 - ((packed + lo16) >> 16)) & 0xffffu : lo16;
+            // (float)c / (float)O correctly rounded: a quotient estimate from
+            // the rounded reciprocal, corrected once by the exact remainder
+            // (Markstein 1990)
+            const float2 d = div[i];
+            const float fc = (float)c, q = fc * d.y;
+            const float ppv = fmaf(fmaf(-q, d.x, fc), d.y, q);
+            const float m = 0.0f - ac.mn[i];
+            float *f = out + (int64_t)(2 * i) * a.s_rows * (MPV ? 3 : 2);
+            if (mine && 2 * i + h < it.n_rows) {
+#if ROCKET_CHECKED
+                if (f < a.S || f + (MPV ? 3 : 2) > a.S + a.s_floats) {
+                    atomicOr(&g_rocket_checks, kCheckStore);
+                    continue;
+                }
+#endif
+                if (MPV) {
+                    f[0] = ppv;
+                    f[1] = m;
+                    f[2] = c > 0 ? ac.ps[i] / fc : 0.0f;
+                } else {
+                    *reinterpret_cast<float2 *>(f) = make_float2(ppv, m);
+                }
+            }
+        }
+    }
+}
+
+template <int V, bool MPV>
+__device__ __forceinline__ void run_series_items(int *next_item, int idx, SplitItem it, int beg, int n_items,
+                                                 const SplitArgs &a, uint32_t lds0, uint32_t plane, int64_t series0,
+                                                 int n_series, int lane, const CheckBounds &cb) {
+    while (idx < n_items) {
+        run_series_item<V, MPV>(it, a, lds0, plane, series0, n_series, lane, cb);
+        int nx = 0;
+        if (lane == 0) nx = atomicAdd(next_item, 1);
+        idx = __builtin_amdgcn_readfirstlane(__shfl(nx, 0, 64));
+        if (idx < n_items) it = load_split_item(as_const(a.items) + as_const(a.order)[beg + idx]);
+    }
+}
+
+constexpr int kSeriesBlock = 256;
+constexpr int kSeriesRounds = 4;  // workgroups per CU a launch splits its items for
+
+template <bool MPV>
+__global__ __launch_bounds__(kSeriesBlock, MPV ? 2 : 3) void rocket_split_series_kernel(SplitArgs a) {
+    extern __shared__ __align__(16) uint32_t smem[];
+    __shared__ int next_item;
+    const int lane = threadIdx.x & (rocket::kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / rocket::kWave);
+    const int64_t b = blockIdx.x;
+    const int xcd = (int)(b % kXcds);
+    const int64_t local = b / kXcds;
+    const int64_t per_variant = a.groups_per_xcd * a.nsplit;
+    const int variant = a.variants[(int)(local / per_variant)];
+    const int64_t rest = local % per_variant;
+    const int64_t group = xcd * a.groups_per_xcd + rest / a.nsplit;
+    const int split = (int)(rest % a.nsplit);
+    const int beg = as_const(a.split_begin)[variant * a.nsplit + split];
+    const int n_items = as_const(a.split_begin)[variant * a.nsplit + split + 1] - beg;
+    const int64_t first = group * rocket::kWave;
+    if (n_items == 0 || first >= a.n_rows) return;
+    const int n_series = (int)min((int64_t)rocket::kWave, a.n_rows - first);
+    const SplitItem it0 =
+        load_split_item(as_const(a.items) + as_const(a.order)[beg + min(wave, n_items - 1)]);
+    // stage: lane = series, so that a position's 64 words are written at once
+    const uint32_t plane = 4u * (uint32_t)a.plane_words;
+    uint32_t *w0 = smem + kSM * rocket::kWave + lane, *w1 = w0 + plane / 4;
+    for (int m = wave; m < 2 * kSM; m += kSeriesBlock / rocket::kWave) {
+        const int pos = m < kSM ? m - kSM : a.L + m - kSM;
+        w0[pos * rocket::kWave] = w1[pos * rocket::kWave] = 0u;
+    }
+    const float *x = a.X + (a.row0 + first + min(lane, n_series - 1)) * (int64_t)a.L;
+    if (a.vec4) {
+        for (int e = wave; e < a.L / 4; e += kSeriesBlock / rocket::kWave) {
+            const float4 v = reinterpret_cast<const float4 *>(x)[e];
+            split_words(v.x, w0[4 * e * rocket::kWave], w1[4 * e * rocket::kWave]);
+            split_words(v.y, w0[(4 * e + 1) * rocket::kWave], w1[(4 * e + 1) * rocket::kWave]);
+            split_words(v.z, w0[(4 * e + 2) * rocket::kWave], w1[(4 * e + 2) * rocket::kWave]);
+            split_words(v.w, w0[(4 * e + 3) * rocket::kWave], w1[(4 * e + 3) * rocket::kWave]);
+        }
+    } else {
+        for (int e = wave; e < a.L; e += kSeriesBlock / rocket::kWave)
+            split_words(x[e], w0[e * rocket::kWave], w1[e * rocket::kWave]);
+    }
+    if (threadIdx.x == 0) next_item = kSeriesBlock / rocket::kWave;
+    __syncthreads();
+    const uint32_t lds0 = (uint32_t)(__UINTPTR_TYPE__)(lds_out *)smem;
+    const CheckBounds cb{lds0 + 2 * plane, nullptr, nullptr};
+    switch (variant) {
+        case 0: run_series_items<0, MPV>(&next_item, wave, it0, beg, n_items, a, lds0, plane, first, n_series, lane, cb); break;
+        case 1: run_series_items<1, MPV>(&next_item, wave, it0, beg, n_items, a, lds0, plane, first, n_series, lane, cb); break;
+        default: run_series_items<2, MPV>(&next_item, wave, it0, beg, n_items, a, lds0, plane, first, n_series, lane, cb); break;
+    }
+}
+
 // Workgroup shapes.  The kernel's registers (164, with MPV 204) allow three
 // wavefronts per SIMD (with MPV two), so a CU holds 12 (8): three workgroups
 // of 256 threads with a third of the 160 KB of LDS each, two of 384, or one of
@@ -552,6 +757,10 @@ hipError_t allow_lds(int device, int64_t limit) {
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)limit);
         if (e != hipSuccess) return e;
     }
+    for (const void *fn : {(const void *)rocket_split_series_kernel<false>, (const void *)rocket_split_series_kernel<true>}) {
+        const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)limit);
+        if (e != hipSuccess) return e;
+    }
     g_lds_allowed[device] = true;
     return hipSuccess;
 }
@@ -571,11 +780,12 @@ struct SplitDevice {
     float *cinit = nullptr;
     int32_t *kid = nullptr, *order = nullptr, *split_begin = nullptr;
     double *inv_O = nullptr;
+    float *div_O = nullptr;
 };
 
 void split_destroy(SplitDevice *d) {
     if (!d) return;
-    void *ptrs[] = {d->items, d->a, d->cinit, d->kid, d->order, d->split_begin, d->inv_O};
+    void *ptrs[] = {d->items, d->a, d->cinit, d->kid, d->order, d->split_begin, d->inv_O, d->div_O};
     for (void *q : ptrs)
         if (q) (void)hipFree(q);
     delete d;
@@ -585,6 +795,52 @@ bool split_fits(int32_t L, int64_t lds_limit) {
     return 2 * 4 * ((int64_t)L + kMargin + kEndZeros) + 256 <= lds_limit;
 }
 
+int64_t split_series_lds(int32_t L) { return 2 * (int64_t)kPosBytes * (L + 2 * kSM); }
+const std::vector<int32_t> &split_slot_kernels(const SplitDevice *d) { return d->host.kid; }
+
+rocket_status split_launch_series(const SplitDevice *d, const float *X, int64_t n, int32_t K, float *S, int64_t s_rows,
+                                  hipStream_t s) {
+    const SplitPlan &P = d->host;
+    const int64_t groups = (n + kWave - 1) / kWave;
+    int64_t present = 0;
+    for (int v = 0; v < kSplitVariants; ++v) present += P.split_begin[v + 1] > P.split_begin[v];
+    // as the fp32 series kernel: about one round of resident workgroups (3 per
+    // CU), with at least two items per wavefront
+    int li = 0;
+    while (li + 1 < kNumSplitLayouts && groups * kSplitCounts[li + 1] * present <= kSeriesRounds * (int64_t)std::max(d->n_cu, 1) &&
+           (int64_t)P.items.size() / present / kSplitCounts[li + 1] >= 2 * (kSeriesBlock / kWave))
+        ++li;
+    SplitArgs a{};
+    a.X = X;
+    a.L = P.L;
+    a.K = K;
+    a.items = d->items;
+    a.a = d->a;
+    a.cinit = d->cinit;
+    a.kid = d->kid;
+    a.inv_O = d->inv_O;
+    a.div_O = d->div_O;
+    a.order = d->order;
+    a.split_begin = d->split_begin + P.layout_off[li];
+    a.nsplit = kSplitCounts[li];
+    const int32_t *sb = P.split_begin.data() + P.layout_off[li];
+    for (int v = kSplitVariants - 1; v >= 0; --v)
+        if (sb[(v + 1) * a.nsplit] > sb[v * a.nsplit]) a.variants[a.n_variants++] = v;
+    a.n_rows = n;
+    a.groups_per_xcd = (groups + kXcds - 1) / kXcds;
+    a.plane_words = (int32_t)(split_series_lds(P.L) / 8);
+    a.vec4 = (P.L % 4 == 0 && ((uintptr_t)X % 16) == 0) ? 1 : 0;
+    a.S = S;
+    a.s_rows = s_rows;
+    a.s_floats = (int64_t)P.kid.size() * s_rows * (d->mpv ? 3 : 2);
+    const unsigned nb = (unsigned)(kXcds * a.groups_per_xcd * a.nsplit * a.n_variants);
+    void *args[] = {&a};
+    const void *fn = d->mpv ? (const void *)rocket_split_series_kernel<true> : (const void *)rocket_split_series_kernel<false>;
+    if (hipLaunchKernel(fn, dim3(nb), dim3(kSeriesBlock), args, (size_t)split_series_lds(P.L), s) != hipSuccess ||
+        hipGetLastError() != hipSuccess)
+        return ROCKET_ERR_HIP;
+    return ROCKET_OK;
+}
 int64_t split_lds_bytes(const SplitDevice *d) { return d->lds; }
 double split_rest_cost(const SplitDevice *d) { return d->host.rest_cost; }
 int split_rows_per_block(const SplitDevice *d) { return d->rows; }
@@ -609,6 +865,7 @@ hipError_t split_create(SplitPlan &&plan, int device, int n_cu, int64_t lds_limi
     if (e == hipSuccess) e = upload(d->host.cinit, &d->cinit);
     if (e == hipSuccess) e = upload(d->host.kid, &d->kid);
     if (e == hipSuccess) e = upload(d->host.inv_O, &d->inv_O);
+    if (e == hipSuccess && d->host.L <= kSeriesMaxL) e = upload(d->host.div_O, &d->div_O);
     if (e == hipSuccess) e = upload(d->host.order, &d->order);
     if (e == hipSuccess) e = upload(d->host.split_begin, &d->split_begin);
     if (e == hipSuccess) e = allow_lds(device, lds_limit - 256);
@@ -622,8 +879,7 @@ hipError_t split_create(SplitPlan &&plan, int device, int n_cu, int64_t lds_limi
 
 rocket_status split_launch(const SplitDevice *d, const float *X, int64_t n, int32_t K, float *F, const FusedArgs *fp32,
                            int64_t fp32_lds, hipStream_t s) {
-    const int block = kShapes[d->mpv ? 1 : 0][d->shape].block, R = d->rows;
-    const int64_t groups = (n + R - 1) / R;
+    const int block = kShapes[d->mpv ? 1 : 0][d->shape].block;
     const SplitPlan &P = d->host;
     int64_t present = 0;
     for (int v = 0; v < kSplitVariants; ++v) present += P.split_begin[v + 1] > P.split_begin[v];
@@ -632,6 +888,11 @@ rocket_status split_launch(const SplitDevice *d, const float *X, int64_t n, int3
     // over, but a few items per wavefront once it is full twice
     const int64_t per_variant = (int64_t)P.items.size() / present;
     const int64_t resident = (int64_t)std::max(d->n_cu, 1) * ((d->mpv ? 512 : 768) / block);
+    // few series: fewer of them per workgroup, down to one, before their items
+    // are split over more workgroups than wavefronts have items for
+    const int64_t spread = std::max<int64_t>(1, n * present / resident);
+    const int R = (int)std::min<int64_t>(d->rows, spread);
+    const int64_t groups = (n + R - 1) / R;
     int li = 0;
     while (li + 1 < kNumSplitLayouts && groups * present * kSplitCounts[li] < 4 * resident &&
            (per_variant / kSplitCounts[li + 1] >= 2 * (block / kWave) ||

@@ -14,6 +14,12 @@ struct SplitDevice;  // a SplitPlan's tables on the device and its launch shape
 bool split_fits(int32_t L, int64_t lds_limit);
 hipError_t split_create(SplitPlan &&plan, int device, int n_cu, int64_t lds_limit, bool mpv, SplitDevice **out);
 void split_destroy(SplitDevice *d);
+// Series-lane layout: LDS per workgroup; the kernel of each slot (-1: empty);
+// S[slot][s_rows] features <- X[n, L], n <= s_rows, asynchronous on s.
+int64_t split_series_lds(int32_t L);
+const std::vector<int32_t> &split_slot_kernels(const SplitDevice *d);
+rocket_status split_launch_series(const SplitDevice *d, const float *X, int64_t n, int32_t K, float *S, int64_t s_rows,
+                                  hipStream_t s);
 int64_t split_lds_bytes(const SplitDevice *d);
 int split_rows_per_block(const SplitDevice *d);
 // Issue cycles per series of the kernels left to fp32 items.

@@ -730,6 +730,8 @@ static const void *toep_fn(int sel) {
     return fns[sel];
 }
 
+constexpr int64_t kNoAllocHalfBytes = (int64_t)32 << 20;  // half of the static scratch (below)
+
 static const void *series_fn(bool mpv) {
     return mpv ? (const void *)rocket_series_kernel<true> : (const void *)rocket_series_kernel<false>;
 }
@@ -740,6 +742,8 @@ struct rocket_plan {
     // kernels run there, the rest in fp32 items of the same launch (Toeplitz
     // items in their own)
     rocket::SplitDevice *split = nullptr;
+    bool split_rest = false;  // some kernels are left to fp32 items
+    int64_t fp32_slots = 0;   // slots of the fp32 items of the whole set (0: few)
     // a split plan's kernel set (host), for the facts of rocket_plan_info,
     // which describe the fp32 items of the whole set
     std::vector<int32_t> k_len, k_dil, k_pad;
@@ -1013,7 +1017,16 @@ extern "C" rocket_status rocket_plan_create_ex(const rocket_kernels *k, int32_t 
             // split items clamp their reads themselves: the flag chooses the
             // layout of the fp32 items beside them
             p->clamp = (flags & ROCKET_PLAN_CLAMPED) != 0;
+            p->split_rest = !rest.items.empty();
             p->host = std::move(rest);
+            // short series: the slots of the whole set's fp32 items bound what
+            // the no-allocation entry takes (at most four per kernel: small
+            // sets always fit)
+            if (L <= kSeriesMaxL && 4 * p->f_cols * (int64_t)sizeof(float) * kSeriesLanes > kNoAllocHalfBytes) {
+                rocket::HostPlan whole;
+                st = rocket::build_host_plan(k, L, &whole);
+                p->fp32_slots = (int64_t)whole.kid.size();
+            }
             try {
                 p->k_len.assign(k->length, k->length + k->n_kernels);
                 p->k_dil.assign(k->dilation, k->dilation + k->n_kernels);
@@ -1038,14 +1051,15 @@ extern "C" rocket_status rocket_plan_create_ex(const rocket_kernels *k, int32_t 
         delete p;
         return st;
     }
-    const bool fp32_items = !p->split || !p->host.items.empty();
+    const bool fp32_items = !p->split || p->split_rest;
     if (!p->direct && fp32_items && !choose_layout(p, (flags & ROCKET_PLAN_CLAMPED) != 0, prop, &lds))
         p->direct = true;
     p->lds_bytes = p->direct ? 0 : lds;
     if (p->series) {
         std::vector<int32_t> slot_of((size_t)k->n_kernels, -1);
-        for (size_t q = 0; q < p->host.kid.size(); ++q)
-            if (p->host.kid[q] >= 0) slot_of[(size_t)p->host.kid[q]] = (int32_t)q;
+        const std::vector<int32_t> &kid = p->split ? rocket::split_slot_kernels(p->split) : p->host.kid;
+        for (size_t q = 0; q < kid.size(); ++q)
+            if (kid[q] >= 0) slot_of[(size_t)kid[q]] = (int32_t)q;
         if (std::find(slot_of.begin(), slot_of.end(), -1) != slot_of.end()) {  // every kernel has a slot
             plan_free_device(p);
             delete p;
@@ -1059,9 +1073,9 @@ extern "C" rocket_status rocket_plan_create_ex(const rocket_kernels *k, int32_t 
         if (e == hipSuccess) e = hipStreamCreateWithFlags(&p->odd, hipStreamNonBlocking);
     }
     if (!p->direct && !p->minirocket &&
-        ((p->split && !p->host.items.empty()) ||
-         std::any_of(p->host.items.begin(), p->host.items.end(),
-                     [](const rocket::ItemDesc &it) { return it.variant >= rocket::kToepVariant0; }))) {
+        (p->split_rest ||
+         (!p->split && std::any_of(p->host.items.begin(), p->host.items.end(),
+                                   [](const rocket::ItemDesc &it) { return it.variant >= rocket::kToepVariant0; })))) {
         for (hipEvent_t *ev : {&p->side_start, &p->side_done})
             if (e == hipSuccess) e = hipEventCreateWithFlags(ev, hipEventDisableTiming);
         if (e == hipSuccess) e = hipStreamCreateWithFlags(&p->side, hipStreamNonBlocking);
@@ -1173,11 +1187,11 @@ extern "C" rocket_status rocket_plan_info(const rocket_plan *p, rocket_plan_fact
         rocket::HostPlan whole;
         const rocket_status st = rocket::build_host_plan(&k, p->host.L, &whole);
         if (st != ROCKET_OK) return st;
-        item_facts(whole, false, false, out);
+        item_facts(whole, p->series, false, out);
     } else {
         item_facts(p->host, p->series, p->minirocket, out);
     }
-    out->lds_bytes = p->series ? p->series_lds : (p->split ? rocket::split_lds_bytes(p->split) : p->lds_bytes);
+    out->lds_bytes = p->series ? (p->split ? rocket::split_series_lds(p->host.L) : p->series_lds) : (p->split ? rocket::split_lds_bytes(p->split) : p->lds_bytes);
     out->direct = p->direct ? 1 : 0;
     out->clamped = p->clamp ? 1 : 0;
     out->features_per_kernel = p->minirocket ? 0 : (p->mpv ? 3 : 2);
@@ -1216,7 +1230,7 @@ static rocket_status launch_direct(const rocket_plan *p, const float *X, int64_t
 // slot column).
 static rocket_status launch_groups(const rocket_plan *p, bool series, const float *X, int64_t n, float *F,
                                    float *S, int64_t s_rows, hipStream_t s) {
-    if (p->split && p->host.items.empty())
+    if (p->split && !p->split_rest)
         return rocket::split_launch(p->split, X, n, p->host.n_kernels, F, nullptr, 0, s);
     // enough workgroups to fill the chip several times over: split the work
     // items of a series across workgroups when there are few series
@@ -1388,9 +1402,10 @@ static rocket_status launch_groups(const rocket_plan *p, bool series, const floa
 // the last permutation.
 
 // Floats of one series' slot-ordered features.
-static int64_t series_slot_row_floats(const rocket_plan *p) {
-    return (int64_t)p->host.kid.size() * (p->mpv ? 3 : 2);
+static int64_t series_slots(const rocket_plan *p) {
+    return (int64_t)(p->split ? rocket::split_slot_kernels(p->split).size() : p->host.kid.size());
 }
+static int64_t series_slot_row_floats(const rocket_plan *p) { return series_slots(p) * (p->mpv ? 3 : 2); }
 
 // Rows per chunk for halves of at most half_bytes (a multiple of 64, at
 // most 8,192 and no more than the call needs); 0 when not even 64 series fit.
@@ -1432,7 +1447,8 @@ static rocket_status enqueue_series(const rocket_plan *p, const float *X, int64_
             st = ROCKET_ERR_HIP;
             break;
         }
-        st = launch_groups(p, true, X + r0 * p->host.L, m, nullptr, Sh, chunk, sh);
+        st = p->split ? rocket::split_launch_series(p->split, X + r0 * p->host.L, m, p->host.n_kernels, Sh, chunk, sh)
+                      : launch_groups(p, true, X + r0 * p->host.L, m, nullptr, Sh, chunk, sh);
         if (st != ROCKET_OK) break;
         if (hipEventRecord(p->half_full[h], sh) != hipSuccess ||
             hipStreamWaitEvent(p->aux, p->half_full[h], 0) != hipSuccess) {
@@ -1450,7 +1466,7 @@ static rocket_status enqueue_series(const rocket_plan *p, const float *X, int64_
         int64_t s_rows = chunk;
         float *Fc = F + r0 * K * nf;
         int64_t mm = m;
-        int32_t n_slots = (int32_t)p->host.kid.size();
+        int32_t n_slots = (int32_t)series_slots(p);
         void *args[] = {(void *)&S, &s_rows, (void *)&slot_of, &K32, (void *)&mm, &Fc, &n_slots};
         if (hipLaunchKernel(pf, grid, dim3(kBlock), args, 0, p->aux) != hipSuccess ||
             hipGetLastError() != hipSuccess || hipEventRecord(p->half_free[h], p->aux) != hipSuccess) {
@@ -1499,7 +1515,7 @@ static rocket_status launch_series(const rocket_plan *p, const float *X, int64_t
 // address that hipGetSymbolAddress returns for the current device, never the
 // array's name (a host-side stand-in).
 // ---------------------------------------------------------------------------
-constexpr size_t kNoAllocScratchBytes = (size_t)64 << 20;  // ROCKET_NOALLOC_SCRATCH_BYTES
+constexpr size_t kNoAllocScratchBytes = 2 * (size_t)kNoAllocHalfBytes;  // ROCKET_NOALLOC_SCRATCH_BYTES
 static_assert(kNoAllocScratchBytes == (size_t)ROCKET_NOALLOC_SCRATCH_BYTES, "header and library agree");
 static __device__ __align__(256) float scratch[kNoAllocScratchBytes / sizeof(float)];
 
@@ -1523,8 +1539,12 @@ static rocket_status noalloc_scratch(int device, float **out) {
 // The series-lane chunk loop over the static scratch (two halves of 32 MiB).
 static rocket_status launch_series_noalloc(const rocket_plan *p, const float *X, int64_t n, float *F,
                                            hipStream_t s, float *buf) {
+    // what fits is decided by the fp32 items' slots; a split plan that needs a
+    // few more runs its tiled layout instead (the same features)
+    const int64_t slots = p->split ? p->fp32_slots : series_slots(p);
+    if (slots * (p->mpv ? 3 : 2) * (int64_t)sizeof(float) * kSeriesLanes > kNoAllocHalfBytes) return ROCKET_ERR_SCRATCH;
     const int64_t chunk = series_chunk_rows(p, n, kNoAllocScratchBytes / 2);
-    if (chunk == 0) return ROCKET_ERR_SCRATCH;
+    if (chunk == 0) return launch_groups(p, false, X, n, F, nullptr, 0, s);
     std::lock_guard<std::mutex> lock(p->scratch_mu);
     return enqueue_series(p, X, n, F, s, buf, chunk);
 }

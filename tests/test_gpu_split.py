@@ -134,3 +134,24 @@ def test_neighbour_rows_do_not_mix(env):
         got = _run(env, ks, Y)
         keep = [0, 2, 3, 5]
         np.testing.assert_array_equal(got[keep], want[keep])
+
+
+@pytest.mark.parametrize("L,n", [(11, 65), (16, 31), (63, 97), (64, 64), (65, 130), (127, 33), (128, 193)])
+def test_series_lane_layout(env, oracle, L, n):
+    """Short series, 32 to a tile: series counts around the 32 of a tile and
+    the 64 of a workgroup, odd and even numbers of positions; the tiled layout
+    of the same kernels gives the same PPV and MAX bit for bit."""
+    _, rk = env
+    K = 1500
+    ks = rk.generate_kernels(4000 + L, K, L)
+    rng = np.random.default_rng(L)
+    X = rng.standard_normal((n, L)).astype(np.float32)
+    ref = oracle.transform(X, ks)
+    for mpv in (False, True):
+        _log("series-lane L=%d n=%d mpv=%s" % (L, n, mpv))
+        F = _run(env, ks, X, mpv=mpv, series=True)
+        _check(F, ref, mpv, "series L=%d" % L)
+        T = _run(env, ks, X, mpv=mpv, tiled=True)
+        nf = 3 if mpv else 2
+        np.testing.assert_array_equal(F[:, 0::nf], T[:, 0::nf])
+        np.testing.assert_array_equal(F[:, 1::nf], T[:, 1::nf])
