@@ -160,11 +160,11 @@ rocket_status build_minirocket_plan(const rocket_minirocket_params *m, HostPlan 
 void build_item_orders(HostPlan &P);
 
 // ---------------------------------------------------------------------------
-// Split items (univariate plans of series longer than kSeriesMaxL): the dot
-// products on v_mfma_f32_32x32x16_bf16, with every fp32 weight and series
+// Split items (univariate plans): the dot products on v_mfma_f32_32x32x16_bf16, with every fp32 weight and series
 // value split into three bf16 parts (8 + 8 + 8 significant bits, so the three
-// parts hold all 24).  Of the nine part products the seven largest are summed
-// (dropped: x2 w3 and x3 w3, below 2^-26 of the product).  An item holds up to
+// parts hold all 24).  Of the nine part products the six largest are summed
+// (dropped: x2 w3 and x3 w2, each at most 2^-24 of the product and about 2^-27
+// in the mean, and x3 w3, below 2^-31).  An item holds up to
 // 32 kernels of one dilation: the rows of the MFMA.  Its columns are 32
 // consecutive positions, its contraction index the taps and their parts.
 //

@@ -1,0 +1,85 @@
+"""The split planner, checked on the CPU: its items, packed fragments, masks,
+clamps and item orders replayed in 64 bits against direct dot products
+(split_replay.cpp), in the tiled and the series-lane layout, over the forms
+that univariate plans accept: every length, centred and other paddings, one to
+33 kernels of a dilation, O down to 1, and generated sets."""
+import ctypes
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+import paper_2601_17091_amd as rk
+from paper_2601_17091_amd import rocket
+from _util import kernel_set
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+CSRC = os.path.join(ROOT, "paper_2601_17091_amd", "csrc")
+
+
+@pytest.fixture(scope="module")
+def replay(tmp_path_factory):
+    gxx = shutil.which("g++")
+    if not gxx:
+        pytest.skip("g++ is needed to build the replay")
+    so = str(tmp_path_factory.mktemp("replay") / "split_replay.so")
+    subprocess.run([gxx, "-std=c++17", "-O2", "-g", "-shared", "-fPIC", "-ffp-contract=off", "-D_GLIBCXX_ASSERTIONS",
+                    "-I", os.path.join(ROOT, "include"), "-I", CSRC, os.path.join(HERE, "split_replay.cpp"),
+                    os.path.join(CSRC, "plan_split.cpp"), os.path.join(CSRC, "plan.cpp"),
+                    os.path.join(CSRC, "generate.cpp"), os.path.join(CSRC, "minirocket.cpp"), "-o", so], check=True)
+    lib = ctypes.CDLL(so)
+
+    def run(ks, L, series, seed=0):
+        x = np.random.default_rng(seed).standard_normal(L).astype(np.float32)
+        c, keep = rocket.as_c_kernels(ks)
+        where, items = ctypes.c_int32(), ctypes.c_int32()
+        rc = lib.split_replay(ctypes.byref(c), L, x.ctypes.data_as(ctypes.POINTER(ctypes.c_float)), int(series),
+                              ctypes.byref(where), ctypes.byref(items))
+        assert rc == 0, "check %d failed at kernel %d" % (rc, where.value)
+        return items.value
+
+    return run
+
+
+@pytest.mark.parametrize("L", [11, 16, 63, 64, 65, 127, 128])
+def test_generated_short(replay, L):
+    ks = rk.generate_kernels(4000 + L, 1500, L)
+    for series in (False, True):
+        assert replay(ks, L, series) > 0
+
+
+@pytest.mark.parametrize("L", [129, 193, 257, 1021, 6465, 20255])
+def test_generated(replay, L):
+    assert replay(rk.generate_kernels(3000 + L, 400 if L < 4000 else 1500, L), L, False) > 0
+
+
+@pytest.mark.parametrize("L", [40, 131, 320])
+def test_lengths_and_paddings(replay, L):
+    rng = np.random.default_rng(L)
+    ln, dil, pad, w = [], [], [], []
+    for d in (1, 2, 3, 12, 13, 26, 39):
+        for length in range(1, 12):
+            for p in rng.integers(0, 41, 1 + (d * length) % 6):
+                if L + 2 * p - (length - 1) * d < 1:
+                    p = (length - 1) * d - L // 2       # O of 1 or 2 and up
+                    p = (p + 1) if L + 2 * p - (length - 1) * d >= 1 else ((length - 1) * d) // 2
+                ln.append(length)
+                dil.append(d)
+                pad.append(int(max(p, 0)))
+                w.append(rng.standard_normal(length))
+    ks = kernel_set(ln, dil, pad, rng.uniform(-1, 1, len(ln)), w)
+    for series in ((False, True) if L <= 128 else (False,)):
+        replay(ks, L, series)
+
+
+@pytest.mark.parametrize("count", [1, 2, 15, 31, 32, 33, 65])
+def test_kernels_per_dilation(replay, count):
+    rng = np.random.default_rng(count)
+    ln = [7, 9, 11] * count
+    pad = [(length - 1) if rng.integers(2) else 0 for length in ln]
+    ks = kernel_set(ln, [2] * len(ln), pad, rng.uniform(-1, 1, len(ln)), [rng.standard_normal(n) for n in ln])
+    for L in (100, 400):
+        replay(ks, L, L == 100)
