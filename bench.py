@@ -3,8 +3,9 @@
 
 One step = one full transform pass over the workload's series (every row,
 every kernel: X[n, L] -> F[n, 2K]) with X already resident in HBM.  Prints
-one JSON line: series x kernels per second, the roofline position of the
-fused kernel (fp32 MFMA bound, 157.3 TFLOP/s peak) and, on the side, the
+one JSON line: series x kernels per second, the algorithmic rate
+against the fp32 peak (157.3 TFLOP/s; univariate sets run their fp32 dot
+products as bf16 part products, which that peak does not bound) and, on the side, the
 fp64 oracle timed on this host's cores over a bounded row sample.
 
     python bench.py [--steps K] [--warmup W] [--workload manufacturing]
@@ -301,8 +302,12 @@ def main():
     # the layout the timed calls ran: series-lane for short univariate series
     # in calls of at least 4,096 series (then a permutation kernel writes F)
     series_path = bool(info.get("series_lane")) and batch >= 4096
-    traffic = None if (args.direct or args.mpv) else traffic_from_profile(
-        w.name, digest, "rocket_series_kernel" if series_path else "rocket_fused_kernel")
+    # univariate workloads: kernel sets this large run split items, whose
+    # instructions the plan's fp32 counts do not describe
+    split = w.channels == 1 and not info["direct"]
+    kernel = ("rocket_split_series_kernel" if split else "rocket_series_kernel") if series_path else (
+        "rocket_split_kernel" if split else "rocket_fused_kernel")
+    traffic = None if (args.direct or args.mpv) else traffic_from_profile(w.name, digest, kernel)
 
     # parity of sampled rows and the CPU baseline on the same rows
     cpu = None
@@ -360,10 +365,10 @@ def main():
         log("parity %s" % parity)
 
     path = "direct" if info["direct"] else ("series-lane-mfma" if series_path else "fused-mfma")
+    if split:
+        path += "-split"
     kernel_name = ("rocket_direct_kernel" if info["direct"] else
-                   ("rocket_series_kernel + rocket_slot_permute_kernel" if series_path else
-                    ("rocket_fused_kernel + rocket_toeplitz_kernel" if info.get("toeplitz_items") else
-                     "rocket_fused_kernel")))
+                   kernel + (" + rocket_slot_permute_kernel" if series_path else ""))
     out = {
         "metric": "series*kernels/s (ROCKET transform, fp32, 1 MI355X)",
         "value": pairs_per_s,
@@ -390,9 +395,9 @@ def main():
                      "algorithmic_flops_per_launch": flops_per_pass / launches,
                      "valid_fma_per_series": valid_per_row,
                      "nominal_fma_per_series": nominal_per_row,
-                     "mfma_fma_issued_per_series": 256 * info["mfma_per_row"],
-                     "valu_fma_issued_per_series": 64 * info.get("valu_fma_per_row", 0),
-                     "mfma_pipe_frac": mfma_fma_issued_frac(mfma_fma_per_pass, ms_per_step),
+                     "mfma_fma_issued_per_series": None if split else 256 * info["mfma_per_row"],
+                     "valu_fma_issued_per_series": None if split else 64 * info.get("valu_fma_per_row", 0),
+                     "mfma_pipe_frac": None if split else mfma_fma_issued_frac(mfma_fma_per_pass, ms_per_step),
                      "hbm_gbps": (traffic / (per_launch_ms * 1e-3) / 1e9) if traffic else None},
         "pass_ms": pass_stats(per_pass),
         "sclk_mhz": clock["mhz"],
