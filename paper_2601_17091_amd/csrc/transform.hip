@@ -1349,7 +1349,15 @@ static rocket_status launch_groups(const rocket_plan *p, bool series, const floa
     // after the caller's earlier work and the call ends on the caller's
     // stream after all of them
     const bool fp32_part = nparts > (toep_part >= 0 ? 1 : 0);
-    const bool side = p->side != nullptr && (toep_part >= 0 ? (fp32_part || p->split) : (p->split && !joined));
+    bool side = p->side != nullptr && (toep_part >= 0 ? (fp32_part || p->split) : (p->split && !joined));
+    // a split plan's call under capture stays on the caller's stream: the side
+    // stream would belong to the capture until it ends, and calls of other
+    // threads on this plan would fail meanwhile
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (side && p->split && s != nullptr) {
+        if (hipStreamIsCapturing(s, &capture) != hipSuccess) return ROCKET_ERR_HIP;
+        side = capture == hipStreamCaptureStatusNone;
+    }
     std::unique_lock<std::mutex> side_lock(p->side_mu, std::defer_lock);
     if (side) {
         side_lock.lock();

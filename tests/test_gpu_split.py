@@ -47,7 +47,7 @@ def _check(F, ref, mpv, what):
 @pytest.mark.parametrize("L", [129, 193, 257, 1021, 3200, 6463, 6464, 6465, 9983, 9984, 9985, 20255, 20300])
 def test_row_lengths(env, oracle, L):
     _, rk = env
-    K = 400 if L < 4000 else 120
+    K = 400 if L < 4000 else 1000   # enough that items of 32 pay at this length
     ks = rk.generate_kernels(3000 + L, K, L)
     rng = np.random.default_rng(L)
     X = rng.standard_normal((5 if L < 4000 else 2, L)).cumsum(1)
@@ -134,6 +134,33 @@ def test_neighbour_rows_do_not_mix(env):
         got = _run(env, ks, Y)
         keep = [0, 2, 3, 5]
         np.testing.assert_array_equal(got[keep], want[keep])
+
+
+@pytest.mark.parametrize("L", [500, 9985])
+def test_captured_call(env, L):
+    """A call under graph capture, in a layout whose fp32 items run beside the
+    split items, and an eager call of the same plan on another stream before
+    the capture ends: both give what an eager call gives, at every replay."""
+    torch, rk = env
+    plan = rk.Plan(rk.generate_kernels(81, 1500, L), L, clamped=True)
+    X = torch.randn((6, L), device="cuda")
+    want = plan.transform(X)
+    F, F2 = torch.zeros_like(want), torch.zeros_like(want)
+    other, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    _log("captured call L=%d" % L)
+    with torch.cuda.graph(graph, capture_error_mode="thread_local"):
+        plan.transform_into(X, F)
+        plan.transform_into(X, F2, stream=other)
+    torch.cuda.synchronize()
+    assert torch.equal(F2, want)
+    for _ in range(3):
+        F.fill_(-1)
+        F2 = plan.transform(X)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(F, want) and torch.equal(F2, want)
 
 
 @pytest.mark.parametrize("L,n", [(11, 65), (16, 31), (63, 97), (64, 64), (65, 130), (127, 33), (128, 193)])
