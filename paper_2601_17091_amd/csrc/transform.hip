@@ -1616,9 +1616,16 @@ extern "C" rocket_status rocket_transform_host(const rocket_plan *p, const float
     const int64_t K2 = p->f_cols;  // floats per feature row
     int64_t B = batch_rows;
     // default: about 8 batches, so copies have neighbours to overlap with,
-    // each within 256 MiB of staging
+    // each within 256 MiB of staging.  Split plans of long rows take 3: a row
+    // computes for longer than its features are copied (both grow with the
+    // kernels, only the first with L; they meet near 1,280 samples), so the
+    // ends of launches count for more than the copies left uncovered (1,000 x
+    // 2,000 samples, 10,000 kernels: 5.08 ms in 8 batches, 3.88 in 3; 200 x
+    // 8,000, 5,000 kernels: 3.79 and 2.90; but 3,000 x 300, 8,000 kernels:
+    // 4.79 and 5.79).
+    const int64_t parts = p->split && L >= 1280 ? 3 : 8;
     if (B == 0)
-        B = std::max<int64_t>(1, std::min<int64_t>((n + 7) / 8, (int64_t)(256 << 20) / ((L + K2) * 4)));
+        B = std::max<int64_t>(1, std::min<int64_t>((n + parts - 1) / parts, (int64_t)(256 << 20) / ((L + K2) * 4)));
     B = std::min(B, n);
     const int64_t nb = (n + B - 1) / B;
     hipStream_t sc = (hipStream_t)hip_stream;
