@@ -31,6 +31,12 @@ static constexpr double kSeriesRowCycles = 1000.0;  // series-lane: an item's st
 // items.
 static constexpr float kMinWeight = 0x1p-64f, kMaxWeight = 0x1p64f;
 
+// The kernels scale a tap's series index to bytes (by 4, in the series-lane
+// layout by 256) before they clamp it.  With at most 65,535 outputs and
+// dilations up to here an index stays below 2^21 in magnitude, its bytes
+// below 2^29; kernels beyond stay on the fp32 items, which clamp first.
+static constexpr int32_t kMaxDilation = 1 << 16;
+
 static uint16_t bf16_rn(float x) {
     uint32_t u;
     std::memcpy(&u, &x, 4);
@@ -58,7 +64,7 @@ static int64_t outputs(const rocket_kernels *k, int32_t i, int64_t L) {
 bool split_eligible(const rocket_kernels *k, int32_t L) {
     if (k->n_channels > 1) return false;
     for (int32_t i = 0; i < k->n_kernels; ++i) {
-        if (outputs(k, i, L) > kSplitMaxOutputs) return false;
+        if (outputs(k, i, L) > kSplitMaxOutputs || k->dilation[i] > kMaxDilation) return false;
         for (int32_t j = 0; j < k->length[i]; ++j) {
             const float w = std::fabs(k->weights[(int64_t)i * k->max_len + j]);
             if (w != 0.0f && !(w >= kMinWeight && w <= kMaxWeight)) return false;

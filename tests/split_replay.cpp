@@ -71,9 +71,13 @@ extern "C" int split_replay(const rocket_kernels *k, int32_t L, const float *x, 
                     const bool edge = b < lo || b >= hi;
                     bool outside = false;
                     auto at = [&](int plane, int tap) -> uint32_t {
-                        int64_t i = (int64_t)it.s0 + n + (int64_t)std::min(tap, it.reach) * it.d + b * block;
-                        if (edge) i = std::min<int64_t>(std::max<int64_t>(i, -margin), L);
-                        i += u * tile;
+                        // bytes in the kernel's 32 bits, as it scales and clamps them
+                        const int scale = 4 * (series ? kWave : 1);
+                        int32_t a = (int32_t)((uint32_t)scale * ((uint32_t)it.s0 + (uint32_t)n +
+                                                                 (uint32_t)std::min(tap, it.reach) * (uint32_t)it.d));
+                        a = (int32_t)((uint32_t)a + (uint32_t)(b * block * scale));
+                        if (edge) a = std::min(std::max(a, -margin * scale), L * scale);
+                        const int64_t i = a / scale + u * tile;
                         outside |= i < -margin || i >= (int64_t)L + margin;
                         return i < 0 || i >= L ? 0u : word[plane][i];
                     };

@@ -182,3 +182,16 @@ def test_series_lane_layout(env, oracle, L, n):
         nf = 3 if mpv else 2
         np.testing.assert_array_equal(F[:, 0::nf], T[:, 0::nf])
         np.testing.assert_array_equal(F[:, 1::nf], T[:, 1::nf])
+
+
+@pytest.mark.parametrize("L,d,kw", [(100, 1 << 24, dict(series=True)), (100, 1 << 24, dict(tiled=True)),
+                                    (100, 1 << 16, dict(series=True)), (500, 1 << 16, {}), (500, 1 << 28, {})])
+def test_far_taps(env, oracle, L, d, kw):
+    """Dilations far beyond the series, with paddings to match: the outer taps
+    of every output read padding."""
+    rng = np.random.default_rng(L)
+    n = 64
+    ks = kernel_set([3] * n, [d] * n, [d] * n, rng.uniform(-1, 1, n), [rng.standard_normal(3) for _ in range(n)])
+    X = rng.standard_normal((70, L)).astype(np.float32)
+    _log("far taps L=%d d=%d %s" % (L, d, kw))
+    _check(_run(env, ks, X, **kw), oracle.transform(X, ks), False, "far taps")

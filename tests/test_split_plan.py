@@ -32,12 +32,14 @@ def replay(tmp_path_factory):
                     os.path.join(CSRC, "generate.cpp"), os.path.join(CSRC, "minirocket.cpp"), "-o", so], check=True)
     lib = ctypes.CDLL(so)
 
-    def run(ks, L, series, seed=0):
+    def run(ks, L, series, seed=0, may_refuse=False):
         x = np.random.default_rng(seed).standard_normal(L).astype(np.float32)
         c, keep = rocket.as_c_kernels(ks)
         where, items = ctypes.c_int32(), ctypes.c_int32()
         rc = lib.split_replay(ctypes.byref(c), L, x.ctypes.data_as(ctypes.POINTER(ctypes.c_float)), int(series),
                               ctypes.byref(where), ctypes.byref(items))
+        if may_refuse and rc == 1:
+            return 0
         assert rc == 0, "check %d failed at kernel %d" % (rc, where.value)
         return items.value
 
@@ -83,3 +85,16 @@ def test_kernels_per_dilation(replay, count):
     ks = kernel_set(ln, [2] * len(ln), pad, rng.uniform(-1, 1, len(ln)), [rng.standard_normal(n) for n in ln])
     for L in (100, 400):
         replay(ks, L, L == 100)
+
+
+@pytest.mark.parametrize("L,d,series", [(100, 1 << 16, True), (100, 1 << 22, True), (128, 1 << 24, True),
+                                        (200, 1 << 16, False), (200, 1 << 28, False), (500, 1 << 30, False)])
+def test_far_taps(replay, L, d, series):
+    """Dilations far beyond the series, with paddings to match: an outer tap
+    reads padding at every output, never the series (a kernel's byte addresses
+    have 32 bits).  Such sets either have right items or run in fp32."""
+    rng = np.random.default_rng(d % 1000003 + L)
+    ln = [3] * 40 + [9 if d < 1 << 28 else 3] * 40
+    pad = [(n - 1) * d // 2 for n in ln]
+    ks = kernel_set(ln, [d] * len(ln), pad, rng.uniform(-1, 1, len(ln)), [rng.standard_normal(n) for n in ln])
+    replay(ks, L, series, may_refuse=d > 1 << 16)
