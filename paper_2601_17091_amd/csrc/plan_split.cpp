@@ -57,6 +57,17 @@ static void split3(float x, uint16_t p[3]) {
     p[2] = bf16_rn(r - bf16_value(p[1]));
 }
 
+// Samples below 2^-110 lose bits in the split (the third part's last bits
+// fall below 2^-133, the smallest bf16), at most 2^-134 each; a sum of such
+// products alone rounds at 2^-149 several times.  Neither shows beside a bias
+// of at least 2^-100 of the weights' sum, whose own rounding is 2^9 times
+// larger; kernels with smaller biases (zero among them) stay on fp32 items.
+static bool bias_carries(const rocket_kernels *k, int32_t i) {
+    float sum = 0.0f;
+    for (int32_t j = 0; j < k->length[i]; ++j) sum += std::fabs(k->weights[(int64_t)i * k->max_len + j]);
+    return std::fabs(k->bias[i]) >= 0x1p-100f * std::max(1.0f, sum);
+}
+
 static int64_t outputs(const rocket_kernels *k, int32_t i, int64_t L) {
     return L + 2 * (int64_t)k->padding[i] - (int64_t)(k->length[i] - 1) * k->dilation[i];
 }
@@ -280,8 +291,7 @@ static void add_item(SplitPlan &P, const Group &g, const rocket_kernels *k, int3
             std::copy(p, p + 3, w[split_matrix_row(q)][f + j]);
             it.reach = std::max(it.reach, f + j);
         }
-        const float b = k->bias[kk];
-        cinit[(q & 1) * (kSplitRows / 2) + q / 2] = b == 0.0f ? 0.0f : -b;
+        cinit[(q & 1) * (kSplitRows / 2) + q / 2] = -k->bias[kk];
         cls[split_matrix_row(q)] = (int)(std::find(g.widths, g.widths + g.n_widths, outputs(k, kk, L)) - g.widths);
     }
     int64_t s0, lo, hi;
@@ -350,9 +360,9 @@ rocket_status build_split_plan(const rocket_kernels *k, int32_t L, SplitPlan *ou
     try {
         SplitPlan P;
         P.L = L;
-        std::map<std::pair<int32_t, bool>, std::vector<Row>> by_dil;
+        std::map<std::pair<int32_t, bool>, std::vector<Row>> by_dil, fp32_only;
         for (int32_t i = 0; i < k->n_kernels; ++i)
-            by_dil[{k->dilation[i], k->length[i] % 2 == 0}].push_back(
+            (bias_carries(k, i) ? by_dil : fp32_only)[{k->dilation[i], k->length[i] % 2 == 0}].push_back(
                 Row{i, ell_index_for(k->length[i]), outputs(k, i, L)});
         // by their own numbers, so that a kernel's item, and with it the
         // rounding of its dot products, does not depend on the set's order
@@ -379,8 +389,14 @@ rocket_status build_split_plan(const rocket_kernels *k, int32_t L, SplitPlan *ou
                 gain += std::max(0.0, g.cost - c);
                 all.push_back(Choice{e.first.first, e.first.second, std::move(g), c});
             }
+        for (const auto &e : fp32_only)
+            for (const Group &g : best_groups(e.second, L, e.first.first, e.first.second)) {
+                P.rest.insert(P.rest.end(), g.slot.begin(), g.slot.end());
+                P.rest_cost += fp32_cycles(g, k, L);
+            }
         // short series: all kernels or none (the series-lane layout runs one
         // kind of item), by the total
+        if (L <= kSeriesMaxL && !P.rest.empty()) all.clear();
         if (L <= kSeriesMaxL) {
             double split = 0.0, fp32 = 0.0;
             for (const Choice &c : all) {

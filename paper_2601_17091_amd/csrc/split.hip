@@ -30,7 +30,8 @@
 // positive y is a set sign bit: one v_perm collects the signs of two rows as
 // 16-bit masks and one v_add3 counts two of those, 0.75 instructions per
 // result register, and MAX is a running minimum (v_min3, half an
-// instruction).  No result is -0: a zero bias starts the sum at +0.
+// instruction).  No result is -0: no bias is zero, and a sum that cancels
+// gives +0.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

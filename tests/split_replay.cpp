@@ -40,6 +40,9 @@ extern "C" int split_replay(const rocket_kernels *k, int32_t L, const float *x, 
         if (i >= 0) ++seen[i];
     for (int32_t i = 0; i < k->n_kernels && *n_items > 0; ++i)
         if (seen[*where = i] != 1) return 3;
+    // biases that could not hide what the split loses of tiny samples
+    for (int32_t i : P.kid)
+        if (i >= 0 && !(std::fabs(k->bias[*where = i]) >= 0x1p-100f)) return 11;
     // every layout of the orders holds every item once, under its own variant
     for (int li = 0; li < kNumSplitLayouts; ++li) {
         const int32_t *sb = P.split_begin.data() + P.layout_off[li];

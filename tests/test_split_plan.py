@@ -98,3 +98,15 @@ def test_far_taps(replay, L, d, series):
     pad = [(n - 1) * d // 2 for n in ln]
     ks = kernel_set(ln, [d] * len(ln), pad, rng.uniform(-1, 1, len(ln)), [rng.standard_normal(n) for n in ln])
     replay(ks, L, series, may_refuse=d > 1 << 16)
+
+
+@pytest.mark.parametrize("L,series", [(100, True), (400, False)])
+def test_tiny_biases(replay, L, series):
+    """Kernels with zero or tiny biases are left to fp32 items (short series:
+    then all are); the others keep theirs."""
+    ks = rk.generate_kernels(11, 1500, L)
+    assert replay(ks, L, series) > 0
+    ks["bias"][::7] = np.array([0.0, -0.0, 1e-40, -1e-31, 2.0 ** -101], np.float32)[np.arange(215) % 5]
+    assert (replay(ks, L, series) > 0) == (L > 128)
+    ks["bias"][:] = 0.0
+    assert replay(ks, L, series) == 0
