@@ -120,7 +120,10 @@ template <bool MPV>
 struct Acc {
     float mn[kRegs];            // running minimum of -y
     uint32_t cnt[kRegs / 2];    // sums of sign masks of rows (2 j, 2 j + 1) in the halves
-    float ps[MPV ? kRegs : 1];  // sum of positive y
+    // sums of positive y, one per tile of a block: chains of O / 64 additions,
+    // as in the fp32 items (one chain of O / 32 had up to 7 % more rounding
+    // error, at 16,384 samples)
+    float ps[2][MPV ? kRegs : 1];
 };
 
 // The word addresses of one block: LDS bytes of the lane's column in tile 0
@@ -194,7 +197,7 @@ __device__ __forceinline__ void block(const Addr<V> &ad, uint32_t plane, const v
         ac.mn[i] = NT == 2 ? fminf(fminf(ac.mn[i], z[0][i]), z[NT - 1][i]) : fminf(ac.mn[i], z[0][i]);
         if (MPV) {
 #pragma unroll
-            for (int u = 0; u < NT; ++u) ac.ps[i] += fmaxf(-z[u][i], 0.0f);
+            for (int u = 0; u < NT; ++u) ac.ps[u][i] += fmaxf(-z[u][i], 0.0f);
         }
     }
 }
@@ -307,7 +310,7 @@ __device__ __forceinline__ void run_split_item(const SplitItem &it, const SplitA
 #pragma unroll
         for (int i = 0; i < kRegs; ++i) {
             ac.mn[i] = INFINITY;
-            if (MPV) ac.ps[i] = 0.0f;
+            if (MPV) ac.ps[0][i] = ac.ps[1][i] = 0.0f;
         }
 #pragma unroll
         for (int j = 0; j < kRegs / 2; ++j) ac.cnt[j] = 0u;
@@ -375,7 +378,7 @@ __device__ __forceinline__ void run_split_item(const SplitItem &it, const SplitA
         if constexpr (MPV) {
             uint32_t p[kRegs];
 #pragma unroll
-            for (int i = 0; i < kRegs; ++i) p[i] = __float_as_uint(ac.ps[i]);
+            for (int i = 0; i < kRegs; ++i) p[i] = __float_as_uint(ac.ps[0][i] + ac.ps[1][i]);
             ps = __uint_as_float(tree<OpFadd>(p, lane));
         }
         if (okid >= 0) {
@@ -562,7 +565,7 @@ __device__ __forceinline__ void run_series_item(const SplitItem &it, const Split
 #pragma unroll
         for (int i = 0; i < kRegs; ++i) {
             ac.mn[i] = INFINITY;
-            if (MPV) ac.ps[i] = 0.0f;
+            if (MPV) ac.ps[0][i] = ac.ps[1][i] = 0.0f;
         }
 #pragma unroll
         for (int j = 0; j < kRegs / 2; ++j) ac.cnt[j] = 0u;
@@ -638,7 +641,7 @@ __device__ __forceinline__ void run_series_item(const SplitItem &it, const Split
                 if (MPV) {
                     f[0] = ppv;
                     f[1] = m;
-                    f[2] = c > 0 ? ac.ps[i] / fc : 0.0f;
+                    f[2] = c > 0 ? (ac.ps[0][i] + ac.ps[1][i]) / fc : 0.0f;
                 } else {
                     *reinterpret_cast<float2 *>(f) = make_float2(ppv, m);
                 }
