@@ -364,14 +364,16 @@ rocket_status build_split_plan(const rocket_kernels *k, int32_t L, SplitPlan *ou
         for (int32_t i = 0; i < k->n_kernels; ++i)
             (bias_carries(k, i) ? by_dil : fp32_only)[{k->dilation[i], k->length[i] % 2 == 0}].push_back(
                 Row{i, ell_index_for(k->length[i]), outputs(k, i, L)});
-        // by their own numbers, so that a kernel's item, and with it the
-        // rounding of its dot products, does not depend on the set's order
+        // by their own numbers (a total order but for equal kernels), so that a
+        // kernel's item, and with it the rounding of its dot products, does not
+        // depend on the set's order
         auto before = [&](const Row &x, const Row &y) {
             if (k->bias[x.k] != k->bias[y.k]) return k->bias[x.k] < k->bias[y.k];
+            if (k->length[x.k] != k->length[y.k]) return k->length[x.k] < k->length[y.k];
+            if (x.O != y.O) return x.O < y.O;
             const float *wx = k->weights + (int64_t)x.k * k->max_len, *wy = k->weights + (int64_t)y.k * k->max_len;
-            const int n = std::min(k->length[x.k], k->length[y.k]);
-            const auto d = std::mismatch(wx, wx + n, wy);
-            return d.first != wx + n ? *d.first < *d.second : x.k < y.k;
+            const auto d = std::mismatch(wx, wx + k->length[x.k], wy);
+            return d.first != wx + k->length[x.k] ? *d.first < *d.second : x.k < y.k;
         };
         for (auto &e : by_dil) std::sort(e.second.begin(), e.second.end(), before);
         struct Choice {

@@ -149,3 +149,13 @@ extern "C" int split_replay(const rocket_kernels *k, int32_t L, const float *x, 
     }
     return 0;
 }
+
+// The slot of every kernel (-1: left to fp32 items).
+extern "C" int split_places(const rocket_kernels *k, int32_t L, int32_t *place) {
+    SplitPlan P;
+    if (build_split_plan(k, L, &P) != ROCKET_OK) return 2;
+    for (int32_t i = 0; i < k->n_kernels; ++i) place[i] = -1;
+    for (size_t q = 0; q < P.kid.size(); ++q)
+        if (P.kid[q] >= 0) place[P.kid[q]] = (int32_t)q;
+    return 0;
+}

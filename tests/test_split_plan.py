@@ -21,7 +21,7 @@ CSRC = os.path.join(ROOT, "paper_2601_17091_amd", "csrc")
 
 
 @pytest.fixture(scope="module")
-def replay(tmp_path_factory):
+def replay_lib(tmp_path_factory):
     gxx = shutil.which("g++")
     if not gxx:
         pytest.skip("g++ is needed to build the replay")
@@ -30,7 +30,12 @@ def replay(tmp_path_factory):
                     "-I", os.path.join(ROOT, "include"), "-I", CSRC, os.path.join(HERE, "split_replay.cpp"),
                     os.path.join(CSRC, "plan_split.cpp"), os.path.join(CSRC, "plan.cpp"),
                     os.path.join(CSRC, "generate.cpp"), os.path.join(CSRC, "minirocket.cpp"), "-o", so], check=True)
-    lib = ctypes.CDLL(so)
+    return ctypes.CDLL(so)
+
+
+@pytest.fixture(scope="module")
+def replay(replay_lib):
+    lib = replay_lib
 
     def run(ks, L, series, seed=0, may_refuse=False):
         x = np.random.default_rng(seed).standard_normal(L).astype(np.float32)
@@ -110,3 +115,34 @@ def test_tiny_biases(replay, L, series):
     assert (replay(ks, L, series) > 0) == (L > 128)
     ks["bias"][:] = 0.0
     assert replay(ks, L, series) == 0
+
+
+@pytest.mark.parametrize("L", [100, 400])
+def test_places_do_not_depend_on_the_order_of_the_set(replay_lib, L):
+    """Kernels that agree in their bias and their first weights (one length a
+    prefix of another), or in all but their padding: each keeps its slot,
+    whatever the order of the set."""
+    rng = np.random.default_rng(L)
+    first = rng.standard_normal(7)
+    ln, pad, w = [], [], []
+    for length in (7, 9, 11):
+        for i in range(60):
+            ln.append(length)
+            pad.append(int(rng.integers(0, 3)) * (length - 1) // 2)
+            w.append(np.concatenate([first, (i // 2) * 0.25 + np.arange(length - 7)]))
+    ks = kernel_set(ln, [1] * len(ln), pad, np.full(len(ln), 0.5), w)
+
+    def places(order):
+        sub = {f: np.ascontiguousarray(ks[f][order]) for f in ("length", "dilation", "padding", "bias", "weights")}
+        c, keep = rocket.as_c_kernels(sub)
+        place = np.empty(len(order), np.int32)
+        assert replay_lib.split_places(ctypes.byref(c), L, place.ctypes.data_as(ctypes.POINTER(ctypes.c_int32))) == 0
+        return place
+
+    # equal kernels may trade places: compare what sits in each slot
+    key = [(ks["length"][i], ks["padding"][i], ks["weights"][i].tobytes()) for i in range(len(ln))]
+    want = {p: key[i] for i, p in enumerate(places(np.arange(len(ln))))}
+    assert len(want) > 32 and -1 not in want
+    for _ in range(5):
+        order = rng.permutation(len(ln))
+        assert {p: key[order[i]] for i, p in enumerate(places(order))} == want
