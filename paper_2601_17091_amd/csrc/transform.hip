@@ -1350,11 +1350,12 @@ static rocket_status launch_groups(const rocket_plan *p, bool series, const floa
     // stream after all of them
     const bool fp32_part = nparts > (toep_part >= 0 ? 1 : 0);
     bool side = p->side != nullptr && (toep_part >= 0 ? (fp32_part || p->split) : (p->split && !joined));
-    // a split plan's call under capture stays on the caller's stream: the side
-    // stream would belong to the capture until it ends, and calls of other
-    // threads on this plan would fail meanwhile
+    // a call under capture stays on the caller's stream: the side stream would
+    // belong to the capture until it ends, calls of other threads on this plan
+    // would fail meanwhile, and destroying the plan would release a stream and
+    // events that take part in it
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    if (side && p->split && s != nullptr) {
+    if (side && s != nullptr) {
         if (hipStreamIsCapturing(s, &capture) != hipSuccess) return ROCKET_ERR_HIP;
         side = capture == hipStreamCaptureStatusNone;
     }

@@ -136,13 +136,17 @@ def test_neighbour_rows_do_not_mix(env):
         np.testing.assert_array_equal(got[keep], want[keep])
 
 
-@pytest.mark.parametrize("L", [500, 9985])
-def test_captured_call(env, L):
+@pytest.mark.parametrize("L,bias", [(500, True), (9985, True), (9985, False)])
+def test_captured_call(env, L, bias):
     """A call under graph capture, in a layout whose fp32 items run beside the
-    split items, and an eager call of the same plan on another stream before
-    the capture ends: both give what an eager call gives, at every replay."""
+    split items (without biases: fp32 and Toeplitz items alone), and an eager
+    call of the same plan on another stream before the capture ends: both give
+    what an eager call gives, at every replay."""
     torch, rk = env
-    plan = rk.Plan(rk.generate_kernels(81, 1500, L), L, clamped=True)
+    ks = rk.generate_kernels(81, 1500 if L < 9985 else 6000, L)
+    if not bias:
+        ks["bias"][:] = 0.0
+    plan = rk.Plan(ks, L, clamped=True)
     X = torch.randn((6, L), device="cuda")
     want = plan.transform(X)
     F, F2 = torch.zeros_like(want), torch.zeros_like(want)
