@@ -881,6 +881,7 @@ hipError_t split_create(SplitPlan &&plan, int device, int n_cu, int64_t lds_limi
     return hipSuccess;
 }
 
+bool split_one_per_cu(const SplitDevice *d) { return d->shape == 2; }
 rocket_status split_launch(const SplitDevice *d, const float *X, int64_t n, int32_t K, float *F, const FusedArgs *fp32,
                            int64_t fp32_lds, hipStream_t s) {
     const int block = kShapes[d->mpv ? 1 : 0][d->shape].block;

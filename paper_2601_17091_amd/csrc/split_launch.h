@@ -22,6 +22,8 @@ rocket_status split_launch_series(const SplitDevice *d, const float *X, int64_t 
                                   hipStream_t s);
 int64_t split_lds_bytes(const SplitDevice *d);
 int split_rows_per_block(const SplitDevice *d);
+// Rows above 40 KB: one workgroup per CU.
+bool split_one_per_cu(const SplitDevice *d);
 // Issue cycles per series of the kernels left to fp32 items.
 double split_rest_cost(const SplitDevice *d);
 // F[n, K * (2 or 3)] of the plan's kernels <- X[n, L], asynchronous on s; rest

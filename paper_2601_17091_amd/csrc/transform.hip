@@ -1337,13 +1337,17 @@ static rocket_status launch_groups(const rocket_plan *p, bool series, const floa
         }
     }
     // Split plans: the MFMA and VALU items run in the split items' launch
-    // while that takes less than a second launch and its events would (about
-    // 30 us), which is while they are short: in that kernel they run 3
-    // wavefronts per SIMD instead of 5, about a quarter slower.  (1,000 series
-    // of 500 samples, 60 us of fp32 items: 667 us in one launch, 704 in two;
-    // 100,000 of 1,000 samples: 132 ms in one, 126 in two; one series: 19 us
-    // against 38.)
-    const bool joined = p->split && !p->clamp && rocket::split_rest_cost(p->split) * (double)n < 1.9e11;
+    // while that costs less than a launch of their own on the side stream and
+    // its events (about 30 us): in that kernel they run 3 wavefronts per SIMD
+    // instead of 5, about a quarter slower.  The bounds are 100 us of the whole
+    // chip (2.4 GHz, 4 SIMDs of 256 CUs), and 400 us for rows above 40 KB,
+    // which run one workgroup per CU.  One launch against two, us: 400 x 1,000
+    // samples, 1,000 kernels (1.3e8 cycles) 114 and 119; 2,000 x 1,000, 300
+    // (3.2e8) 268 and 229; 400 x 5,000, 5,000 (1e9) 2,054 and 1,943; 100,000 x
+    // 1,000, 10,000 (4e10) 126,200 and 123,500; 16 x 16,000, 10,000 (7.5e8) 502
+    // and 594; 400 x 16,000, 1,000 (2.4e9) 2,171 and 2,085.
+    const double rest_cycles = p->split ? rocket::split_rest_cost(p->split) * (double)n : 0.0;
+    const bool joined = p->split && !p->clamp && rest_cycles < (rocket::split_one_per_cu(p->split) ? 1e9 : 2.5e8);
     // Toeplitz items, and the fp32 items of a split plan's long calls, run on
     // the plan's side stream, concurrently with the other part: they start
     // after the caller's earlier work and the call ends on the caller's
