@@ -34,7 +34,8 @@ struct FusedArgs {
     int32_t nsplit;
     int32_t n_variants;          // variants that have items, launched variant-major
     int32_t variants[kNumVariants];
-    int64_t groups_per_xcd;      // row groups (of rows_per_block series) per XCD
+    int32_t xcd_shift;           // workgroup b belongs to XCD share b mod 2^xcd_shift (3: its XCD; 0: one share)
+    int64_t groups_per_xcd;      // row groups (of rows_per_block series) per share
     int32_t halo_lo;
     int32_t row_stride;
     int32_t tail_pad;        // zero floats staged after the last row
@@ -441,6 +442,7 @@ namespace {
 
 constexpr int kMaxRowsPerBlock = 7;
 constexpr int kXcds = 8;          // MI355X: 8 XCDs, workgroups dealt round-robin
+constexpr int kXcdShift = 3;
 constexpr int kTile = rocket::kTile;
 
 // DPP controls (GFX9 encoding)
@@ -1400,8 +1402,8 @@ struct GroupWork {
 // one code variant at a time.  Returns false when the workgroup has nothing
 // to do (uniformly for the whole workgroup).
 __device__ __forceinline__ bool group_work(const FusedArgs &a, int64_t b, GroupWork &w) {
-    const int xcd = (int)(b % kXcds);
-    const int64_t local = b / kXcds;
+    const int xcd = (int)b & ((1 << a.xcd_shift) - 1);
+    const int64_t local = b >> a.xcd_shift;
     const int64_t per_variant = a.groups_per_xcd * a.nsplit;
     const int vi = (int)(local / per_variant);
     const int64_t rest = local % per_variant;

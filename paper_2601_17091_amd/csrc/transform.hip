@@ -1386,6 +1386,7 @@ static rocket_status launch_groups(const rocket_plan *p, bool series, const floa
             const int64_t groups_now = (q.n_rows + R - 1) / R;
             q.groups_per_xcd = (groups_now + kXcds - 1) / kXcds;
             const unsigned nb = (unsigned)(kXcds * q.groups_per_xcd * nsplit * q.n_variants);
+            q.xcd_shift = kXcdShift;
             void *args[] = {&q};
             if (hipLaunchKernel(fns[part], dim3(nb), dim3(big ? kBigBlock : kBlock), args, lds, sq) != hipSuccess ||
                 hipGetLastError() != hipSuccess) {
