@@ -274,10 +274,11 @@ __device__ __forceinline__ void load_fragments(const SplitItem &it, const SplitA
 
 constexpr int kTileBytes = 4 * rocket::kSplitTile;
 
-// One item over the staged series.
+// One item over the staged series r0, r0 + r_step, ...
 template <int V, bool MPV>
 __device__ __forceinline__ void run_split_item(const SplitItem &it, const SplitArgs &a, uint32_t lds0, uint32_t plane,
-                                         int nrows, float *F0, int lane, const CheckBounds &cb) {
+                                               int r0, int r_step, int nrows, float *F0, int lane,
+                                               const CheckBounds &cb) {
     const int n = lane & 31, h = lane >> 5;
     v4u fa[rocket::kSplitFrags[V]];
     v16f cinit;
@@ -304,7 +305,7 @@ __device__ __forceinline__ void run_split_item(const SplitItem &it, const SplitA
     const int wa = (V > 0 && h) ? it.width[2] : it.width[0], wb = (V > 0 && h) ? it.width[3] : it.width[1];
     const int64_t f_stride = (int64_t)(MPV ? 3 : 2) * a.K;
     const uint32_t zero = lds0 + 4u * (uint32_t)(nrows * a.pitch + n);
-    for (int r = 0; r < nrows; ++r) {
+    for (int r = r0; r < nrows; r += r_step) {
         const uint32_t row = lds0 + 4u * (uint32_t)(kMargin + r * a.pitch);  // series index 0
         const uint32_t row_tail = row + (V == 2 ? (uint32_t)h * plane : 0u);
         Acc<MPV> ac;
@@ -425,19 +426,28 @@ __device__ __forceinline__ SplitItem load_split_item(ConstPtr<SplitItem> p) {
     return it;
 }
 
-// The items of one variant: a wavefront's first is its own number's (it, read
-// by the caller while the series were staged), the others come from the
-// workgroup's counter.
+// A workgroup of few items deals each of them to its wavefronts in 2^sh parts
+// of its series (rows do not interact), so that no wavefront goes without.
+__device__ __forceinline__ int part_shift(int n_items, int n_rows, int n_waves) {
+    int sh = 0;
+    while (sh < 2 && (n_items << sh) < 2 * n_waves && (1 << sh) < n_rows) ++sh;
+    return sh;
+}
+
+// The tasks (item, part) of one variant: a wavefront's first is its own
+// number's (it, read by the caller while the series were staged), the others
+// come from the workgroup's counter.
 template <int V, bool MPV>
-__device__ __forceinline__ void run_split_items(int *next_item, int idx, SplitItem it, int beg, int n_items,
+__device__ __forceinline__ void run_split_items(int *next_item, int idx, SplitItem it, int beg, int n_items, int sh,
                                                 const SplitArgs &a, uint32_t lds0, uint32_t plane, int nrows, float *F0,
                                                 int lane, const CheckBounds &cb) {
-    while (idx < n_items) {
-        run_split_item<V, MPV>(it, a, lds0, plane, nrows, F0, lane, cb);
+    const int n_tasks = n_items << sh, parts = 1 << sh;
+    while (idx < n_tasks) {
+        run_split_item<V, MPV>(it, a, lds0, plane, idx & (parts - 1), parts, nrows, F0, lane, cb);
         int nx = 0;
         if (lane == 0) nx = atomicAdd(next_item, 1);
         idx = __builtin_amdgcn_readfirstlane(__shfl(nx, 0, 64));
-        if (idx < n_items) it = load_split_item(as_const(a.items) + as_const(a.order)[beg + idx]);
+        if (idx < n_tasks) it = load_split_item(as_const(a.items) + as_const(a.order)[beg + (idx >> sh)]);
     }
 }
 
@@ -511,8 +521,9 @@ __global__ __launch_bounds__(BLOCK, MPV ? 2 : 3) void rocket_split_kernel(SplitA
     const int64_t grow = a.row0 + first;
     const uint32_t plane = PLANE ? (uint32_t)PLANE : 4u * (uint32_t)a.plane_words;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / rocket::kWave);
+    const int sh = part_shift(n_items, nrows, BLOCK / rocket::kWave);
     const SplitItem it0 =
-        load_split_item(as_const(a.items) + as_const(a.order)[beg + min(wave, n_items - 1)]);
+        load_split_item(as_const(a.items) + as_const(a.order)[beg + min(wave >> sh, n_items - 1)]);
     stage_rows<BLOCK>(a, a.X + grow * a.L, nrows, smem, smem + plane / 4);
     if (threadIdx.x == 0) next_item = BLOCK / rocket::kWave;
     __syncthreads();
@@ -522,9 +533,9 @@ __global__ __launch_bounds__(BLOCK, MPV ? 2 : 3) void rocket_split_kernel(SplitA
                    a.F + (a.row0 + a.n_rows) * f_row};
     float *F0 = a.F + grow * f_row;
     switch (variant) {
-        case 0: run_split_items<0, MPV>(&next_item, wave, it0, beg, n_items, a, lds0, plane, nrows, F0, lane, cb); break;
-        case 1: run_split_items<1, MPV>(&next_item, wave, it0, beg, n_items, a, lds0, plane, nrows, F0, lane, cb); break;
-        default: run_split_items<2, MPV>(&next_item, wave, it0, beg, n_items, a, lds0, plane, nrows, F0, lane, cb); break;
+        case 0: run_split_items<0, MPV>(&next_item, wave, it0, beg, n_items, sh, a, lds0, plane, nrows, F0, lane, cb); break;
+        case 1: run_split_items<1, MPV>(&next_item, wave, it0, beg, n_items, sh, a, lds0, plane, nrows, F0, lane, cb); break;
+        default: run_split_items<2, MPV>(&next_item, wave, it0, beg, n_items, sh, a, lds0, plane, nrows, F0, lane, cb); break;
     }
 }
 
@@ -542,7 +553,8 @@ constexpr int kSM = rocket::kSplitSeriesMargin;
 
 template <int V, bool MPV>
 __device__ __forceinline__ void run_series_item(const SplitItem &it, const SplitArgs &a, uint32_t lds0, uint32_t plane,
-                                                int64_t series0, int n_series, int lane, const CheckBounds &cb) {
+                                                int64_t series0, int first, int n_series, int lane,
+                                                const CheckBounds &cb) {
     const int n = lane & 31, h = lane >> 5;
     v4u fa[rocket::kSplitFrags[V]];
     v16f cinit;
@@ -553,7 +565,7 @@ __device__ __forceinline__ void run_series_item(const SplitItem &it, const Split
     constexpr int kUnroll = MPV ? 1 : 2;
     constexpr uint32_t step = kUnroll * 2 * kPosBytes;
     const uint32_t step3 = idle ? 0u : step;
-    for (int s0 = 0; s0 < n_series; s0 += rocket::kSplitTile) {
+    for (int s0 = first; s0 < n_series; s0 += rocket::kSplitTile) {
         const int base = (int)lds0 + kSM * kPosBytes + 4 * (s0 + n);  // position 0
         const uint32_t zero = (uint32_t)(base - kSM * kPosBytes);
         int main0[4], tail0[3];
@@ -651,16 +663,21 @@ __device__ __forceinline__ void run_series_item(const SplitItem &it, const Split
     }
 }
 
+// The tasks of one variant, as run_split_items: items, or where those are few
+// (sh = 1) items x the workgroup's two tiles of 32 series.
 template <int V, bool MPV>
-__device__ __forceinline__ void run_series_items(int *next_item, int idx, SplitItem it, int beg, int n_items,
+__device__ __forceinline__ void run_series_items(int *next_item, int idx, SplitItem it, int beg, int n_items, int sh,
                                                  const SplitArgs &a, uint32_t lds0, uint32_t plane, int64_t series0,
                                                  int n_series, int lane, const CheckBounds &cb) {
-    while (idx < n_items) {
-        run_series_item<V, MPV>(it, a, lds0, plane, series0, n_series, lane, cb);
+    const int n_tasks = n_items << sh;
+    while (idx < n_tasks) {
+        const int first = sh ? (idx & 1) * rocket::kSplitTile : 0;
+        run_series_item<V, MPV>(it, a, lds0, plane, series0, first,
+                                sh ? min(n_series, first + rocket::kSplitTile) : n_series, lane, cb);
         int nx = 0;
         if (lane == 0) nx = atomicAdd(next_item, 1);
         idx = __builtin_amdgcn_readfirstlane(__shfl(nx, 0, 64));
-        if (idx < n_items) it = load_split_item(as_const(a.items) + as_const(a.order)[beg + idx]);
+        if (idx < n_tasks) it = load_split_item(as_const(a.items) + as_const(a.order)[beg + (idx >> sh)]);
     }
 }
 
@@ -686,8 +703,9 @@ __global__ __launch_bounds__(kSeriesBlock, MPV ? 2 : 3) void rocket_split_series
     const int64_t first = group * rocket::kWave;
     if (n_items == 0 || first >= a.n_rows) return;
     const int n_series = (int)min((int64_t)rocket::kWave, a.n_rows - first);
+    const int sh = n_items < 2 * (kSeriesBlock / rocket::kWave) ? 1 : 0;
     const SplitItem it0 =
-        load_split_item(as_const(a.items) + as_const(a.order)[beg + min(wave, n_items - 1)]);
+        load_split_item(as_const(a.items) + as_const(a.order)[beg + min(wave >> sh, n_items - 1)]);
     // stage: lane = series, so that a position's 64 words are written at once
     const uint32_t plane = 4u * (uint32_t)a.plane_words;
     uint32_t *w0 = smem + kSM * rocket::kWave + lane, *w1 = w0 + plane / 4;
@@ -713,9 +731,9 @@ __global__ __launch_bounds__(kSeriesBlock, MPV ? 2 : 3) void rocket_split_series
     const uint32_t lds0 = (uint32_t)(__UINTPTR_TYPE__)(lds_out *)smem;
     const CheckBounds cb{lds0 + 2 * plane, nullptr, nullptr};
     switch (variant) {
-        case 0: run_series_items<0, MPV>(&next_item, wave, it0, beg, n_items, a, lds0, plane, first, n_series, lane, cb); break;
-        case 1: run_series_items<1, MPV>(&next_item, wave, it0, beg, n_items, a, lds0, plane, first, n_series, lane, cb); break;
-        default: run_series_items<2, MPV>(&next_item, wave, it0, beg, n_items, a, lds0, plane, first, n_series, lane, cb); break;
+        case 0: run_series_items<0, MPV>(&next_item, wave, it0, beg, n_items, sh, a, lds0, plane, first, n_series, lane, cb); break;
+        case 1: run_series_items<1, MPV>(&next_item, wave, it0, beg, n_items, sh, a, lds0, plane, first, n_series, lane, cb); break;
+        default: run_series_items<2, MPV>(&next_item, wave, it0, beg, n_items, sh, a, lds0, plane, first, n_series, lane, cb); break;
     }
 }
 
@@ -728,6 +746,16 @@ struct Shape {
     int plane;  // bytes of a plane; 0: given at run time
 };
 constexpr Shape kShapes[2][3] = {{{256, 26624}, {384, 40704}, {768, 0}}, {{256, 40704}, {256, 40704}, {512, 0}}};
+
+// Row groups go to the XCDs in equal shares, unless that would leave a fifth of
+// the chip without work (one series would run on one XCD alone): then the
+// workgroups are dealt to the XCDs one by one.  One series, us: 500 samples,
+// 10,000 kernels 15.3 -> 9.0, 16,000 samples 513 -> 180; with balanced shares
+// (16 and 50 series of 64 to 200 samples) the shares measured 5 % faster.
+int32_t xcd_shift(int64_t groups) {
+    const int64_t slots = (groups + kXcds - 1) / kXcds * kXcds;
+    return 5 * groups < 4 * slots ? 0 : kXcdShift;
+}
 
 const void *kernel_fn(int shape, bool mpv) {
     if (mpv)
@@ -747,16 +775,6 @@ hipError_t upload(const std::vector<T> &h, T **d) {
     if (e == hipSuccess) e = hipMemcpy(*d, h.data(), h.size() * sizeof(T), hipMemcpyHostToDevice);
     return e;
 }
-// Row groups go to the XCDs in equal shares, unless that would leave a fifth of
-// the chip without work (one series would run on one XCD alone): then the
-// workgroups are dealt to the XCDs one by one.  One series, us: 500 samples,
-// 10,000 kernels 15.3 -> 9.0, 16,000 samples 513 -> 180; with balanced shares
-// (16 and 50 series of 64 to 200 samples) the shares measured 5 % faster.
-int32_t xcd_shift(int64_t groups) {
-    const int64_t slots = (groups + kXcds - 1) / kXcds * kXcds;
-    return 5 * groups < 4 * slots ? 0 : kXcdShift;
-}
-
 
 constexpr int kMaxDevices = 64;
 std::mutex g_lds_mu;
@@ -819,11 +837,15 @@ rocket_status split_launch_series(const SplitDevice *d, const float *X, int64_t 
     const int64_t groups = (n + kWave - 1) / kWave;
     int64_t present = 0;
     for (int v = 0; v < kSplitVariants; ++v) present += P.split_begin[v + 1] > P.split_begin[v];
-    // as the fp32 series kernel: about one round of resident workgroups (3 per
-    // CU), with at least two items per wavefront
+    // at most kSeriesRounds workgroups per CU (LDS and registers let two to
+    // three run at once), with at least two items per wavefront once every CU
+    // has a workgroup (5,000 series of 128 samples, 1,000 kernels: 322 us with
+    // that bound at any size, 200 now)
+    const int64_t n_cu = std::max(d->n_cu, 1);
     int li = 0;
-    while (li + 1 < kNumSplitLayouts && groups * kSplitCounts[li + 1] * present <= kSeriesRounds * (int64_t)std::max(d->n_cu, 1) &&
-           (int64_t)P.items.size() / present / kSplitCounts[li + 1] >= 2 * (kSeriesBlock / kWave))
+    while (li + 1 < kNumSplitLayouts && groups * kSplitCounts[li + 1] * present <= kSeriesRounds * n_cu &&
+           ((int64_t)P.items.size() / present / kSplitCounts[li + 1] >= 2 * (kSeriesBlock / kWave) ||
+            groups * present * kSplitCounts[li] < n_cu))
         ++li;
     SplitArgs a{};
     a.X = X;
@@ -859,6 +881,7 @@ rocket_status split_launch_series(const SplitDevice *d, const float *X, int64_t 
 int64_t split_lds_bytes(const SplitDevice *d) { return d->lds; }
 double split_rest_cost(const SplitDevice *d) { return d->host.rest_cost; }
 int split_rows_per_block(const SplitDevice *d) { return d->rows; }
+bool split_one_per_cu(const SplitDevice *d) { return d->shape == 2; }
 
 hipError_t split_create(SplitPlan &&plan, int device, int n_cu, int64_t lds_limit, bool mpv, SplitDevice **out) {
     *out = nullptr;
@@ -892,7 +915,6 @@ hipError_t split_create(SplitPlan &&plan, int device, int n_cu, int64_t lds_limi
     return hipSuccess;
 }
 
-bool split_one_per_cu(const SplitDevice *d) { return d->shape == 2; }
 rocket_status split_launch(const SplitDevice *d, const float *X, int64_t n, int32_t K, float *F, const FusedArgs *fp32,
                            int64_t fp32_lds, hipStream_t s) {
     const int block = kShapes[d->mpv ? 1 : 0][d->shape].block;
