@@ -280,14 +280,14 @@ static rocket_status build_plan(const rocket_kernels *k, int32_t L, bool allow_t
 
 // Toeplitz items run in a launch of their own, which stages every row group
 // again: they are kept only where they carry a real share of the work (at
-// least kToepMinShare of the items' cost), else their kernels stay in VALU
-// items.
+// least kToepMinShare of the cost of the items and of what runs beside them),
+// else their kernels stay in VALU items.
 constexpr double kToepMinShare = 0.03;
 
-rocket_status build_host_plan(const rocket_kernels *k, int32_t L, HostPlan *out) {
+rocket_status build_host_plan(const rocket_kernels *k, int32_t L, HostPlan *out, double beside) {
     rocket_status st = build_plan(k, L, true, out);
     if (st != ROCKET_OK) return st;
-    double toep = 0.0, total = 0.0;
+    double toep = 0.0, total = beside;
     for (const ItemDesc &it : out->items) {
         total += it.cost;
         if (it.variant >= kToepVariant0) toep += it.cost;

@@ -148,7 +148,9 @@ struct HostPlan {
 rocket_status validate_kernels(const rocket_kernels *k, int32_t L);
 
 // Build the host-side tables of a plan.  Assumes validate_kernels passed.
-rocket_status build_host_plan(const rocket_kernels *k, int32_t L, HostPlan *out);
+// beside: what else a call runs per series, in MFMAs (split items, which
+// decide whether Toeplitz items pay their launch).
+rocket_status build_host_plan(const rocket_kernels *k, int32_t L, HostPlan *out, double beside = 0.0);
 
 // MINIROCKET parameters: validation and the plan's host tables.
 rocket_status validate_minirocket(const rocket_minirocket_params *m);

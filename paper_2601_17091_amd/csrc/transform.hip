@@ -929,9 +929,10 @@ static void item_facts(const rocket::HostPlan &host, bool series, bool minirocke
             if (it.variant >= rocket::kToepVariant0) ++f->toeplitz_items;
 }
 
-// The fp32 plan of the kernels `rest` of a set (their ids as in the set).
+// The fp32 plan of the kernels `rest` of a set (their ids as in the set), beside
+// split items of split_cost issue cycles (8.7 to an fp32 MFMA) per series.
 static rocket_status build_rest_plan(const rocket_kernels *k, int32_t L, const std::vector<int32_t> &rest,
-                                     rocket::HostPlan *out) {
+                                     double split_cost, rocket::HostPlan *out) {
     try {
         rocket::HostPlan P;
         P.L = L;
@@ -953,7 +954,7 @@ static rocket_status build_rest_plan(const rocket_kernels *k, int32_t L, const s
             sub.padding = pad.data();
             sub.bias = bias.data();
             sub.weights = w.data();
-            const rocket_status st = rocket::build_host_plan(&sub, L, &P);
+            const rocket_status st = rocket::build_host_plan(&sub, L, &P, split_cost / 8.7);
             if (st != ROCKET_OK) return st;
             for (int32_t &q : P.kid)
                 if (q >= 0) q = rest[(size_t)q];
@@ -1012,7 +1013,7 @@ extern "C" rocket_status rocket_plan_create_ex(const rocket_kernels *k, int32_t 
         rocket::SplitPlan sp;
         rocket::HostPlan rest;
         st = rocket::build_split_plan(k, L, &sp);
-        if (st == ROCKET_OK) st = build_rest_plan(k, L, sp.rest, &rest);
+        if (st == ROCKET_OK) st = build_rest_plan(k, L, sp.rest, sp.cost, &rest);
         if (st == ROCKET_OK && !sp.items.empty()) {
             // split items clamp their reads themselves: the flag chooses the
             // layout of the fp32 items beside them
@@ -1384,9 +1385,9 @@ static rocket_status launch_groups(const rocket_plan *p, bool series, const floa
             q.row0 = r0;
             q.n_rows = std::min<int64_t>(max_rows, n - r0);
             const int64_t groups_now = (q.n_rows + R - 1) / R;
+            q.xcd_shift = kXcdShift;
             q.groups_per_xcd = (groups_now + kXcds - 1) / kXcds;
             const unsigned nb = (unsigned)(kXcds * q.groups_per_xcd * nsplit * q.n_variants);
-            q.xcd_shift = kXcdShift;
             void *args[] = {&q};
             if (hipLaunchKernel(fns[part], dim3(nb), dim3(big ? kBigBlock : kBlock), args, lds, sq) != hipSuccess ||
                 hipGetLastError() != hipSuccess) {
