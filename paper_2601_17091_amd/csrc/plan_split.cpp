@@ -354,7 +354,32 @@ static void add_item(SplitPlan &P, const Group &g, const rocket_kernels *k, int3
 // this share of the pass (they stage the series again, in workgroups or a
 // launch of their own).
 static constexpr double kRestMinGain = 0.02;
-static constexpr double kShortGain = 0.85;  // short series take split items below this share of the fp32 items' cost
+// Short series take split items below this share of the fp32 items' cost: 300
+// kernels x 100 samples (0.8) run 5,000 to 100,000 series at 0.79 to 0.91 of
+// the fp32 items' speed, 500 x 128 (0.69) at 1.07 to 1.12, 300 x 64 (0.69) at
+// 1.05 to 1.10.
+static constexpr double kShortGain = 0.78;
+
+// Sets of few kernels leave the wavefronts of a split workgroup without items
+// (it stages its series for each of three variants), and their rest is most of
+// the work: below these bounds the fp32 plan of the whole set is the faster one
+// somewhere between 16 and 100,000 series, by up to a quarter.  Speed against
+// that plan at many (1,000) series: 200 kernels x 300 samples (3 items, gain
+// 1.16) 1.12 (0.80); 300 x 500 (6, 1.16) 1.10 (0.91); 500 x 500 (13, 1.26) 1.19
+// (1.03); 1,000 x 4,000 (18, 1.18) 1.15 (1.17).  With MPV (two wavefronts per
+// SIMD): 500 x 500 1.03 (0.79), 1,000 x 2,000 (22, 1.22) 1.04 (1.02, 100 series
+// 0.81), 1,000 x 500 (27, 1.42) 1.12 (0.96), 2,000 x 5,000 (1.27) 1.08 (1.06).
+// Above 10,000 samples any split items pay with many series (150 kernels 1.07,
+// 1,000 kernels 1.05 at 16,000 samples; 200 x 12,000 1.27).
+static constexpr double kSplitMinGain = 1.15, kSplitMinGainMpv = 1.25;
+static constexpr size_t kSplitMinItems = 12, kSplitMinItemsMpv = 20;
+
+bool split_pays(const SplitPlan &P, bool mpv) {
+    if (P.items.empty()) return false;
+    if (P.L <= kSeriesMaxL || P.L > 10000) return true;
+    return P.items.size() >= (mpv ? kSplitMinItemsMpv : kSplitMinItems) &&
+           P.fp32_cost >= (mpv ? kSplitMinGainMpv : kSplitMinGain) * (P.cost + P.rest_cost);
+}
 
 rocket_status build_split_plan(const rocket_kernels *k, int32_t L, SplitPlan *out) {
     try {
@@ -388,13 +413,16 @@ rocket_status build_split_plan(const rocket_kernels *k, int32_t L, SplitPlan *ou
             for (Group &g : best_groups(e.second, L, e.first.first, e.first.second)) {
                 const double c = fp32_cycles(g, k, L);
                 total += std::min(g.cost, c);
+                P.fp32_cost += c;
                 gain += std::max(0.0, g.cost - c);
                 all.push_back(Choice{e.first.first, e.first.second, std::move(g), c});
             }
         for (const auto &e : fp32_only)
             for (const Group &g : best_groups(e.second, L, e.first.first, e.first.second)) {
                 P.rest.insert(P.rest.end(), g.slot.begin(), g.slot.end());
-                P.rest_cost += fp32_cycles(g, k, L);
+                const double c = fp32_cycles(g, k, L);
+                P.rest_cost += c;
+                P.fp32_cost += c;
             }
         // short series: all kernels or none (the series-lane layout runs one
         // kind of item), by the total

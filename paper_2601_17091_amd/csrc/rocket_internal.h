@@ -239,6 +239,7 @@ struct SplitPlan {
     std::vector<int32_t> rest;    // kernels left to the fp32 items (ascending)
     double cost = 0.0;            // issue cycles per series of the items
     double rest_cost = 0.0;       // and of the rest as fp32 items
+    double fp32_cost = 0.0;       // and of all kernels as fp32 items
 };
 
 // Whether a kernel set can run as split items on series of length L.
@@ -246,6 +247,8 @@ bool split_eligible(const rocket_kernels *k, int32_t L);
 // Groups the kernels into split items; those that fp32 items run faster are
 // left in `rest` when together they carry a real share of the work.
 rocket_status build_split_plan(const rocket_kernels *k, int32_t L, SplitPlan *out);
+// Whether a plan with split items beats the fp32 plan of the whole set.
+bool split_pays(const SplitPlan &P, bool mpv);
 
 // Item orders of items given by variant and cost (see build_item_orders).
 void order_items(const std::vector<int32_t> &variant, const std::vector<int32_t> &cost, int n_variants,

@@ -1013,8 +1013,9 @@ extern "C" rocket_status rocket_plan_create_ex(const rocket_kernels *k, int32_t 
         rocket::SplitPlan sp;
         rocket::HostPlan rest;
         st = rocket::build_split_plan(k, L, &sp);
-        if (st == ROCKET_OK) st = build_rest_plan(k, L, sp.rest, sp.cost, &rest);
-        if (st == ROCKET_OK && !sp.items.empty()) {
+        const bool pays = st == ROCKET_OK && rocket::split_pays(sp, p->mpv);
+        if (pays) st = build_rest_plan(k, L, sp.rest, sp.cost, &rest);
+        if (st == ROCKET_OK && pays) {
             // split items clamp their reads themselves: the flag chooses the
             // layout of the fp32 items beside them
             p->clamp = (flags & ROCKET_PLAN_CLAMPED) != 0;

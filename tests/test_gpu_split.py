@@ -217,3 +217,26 @@ def test_tiny_samples(env, L, kw):
     a, b = _run(env, ks, X, **kw), _run(env, ks, np.ldexp(X, -120).astype(np.float32), **kw)
     back = np.ldexp(b[:, 1::2].astype(np.float64), 120)
     np.testing.assert_allclose(back, a[:, 1::2], rtol=0, atol=11 * 2.0 ** -20)
+
+
+# 300: a few items per workgroup, dealt to its wavefronts in parts, and over
+# all XCDs in the short calls; 2,000: the long call's fp32 items run beside the
+# split items, the short calls' in their launch; 11,000: one workgroup per CU;
+# 64: series-lane, half the series of a workgroup at a time
+@pytest.mark.parametrize("L,K,n,mpv", [(300, 600, 3000, False), (300, 2000, 700, True), (2000, 1000, 500, False),
+                                       (2000, 5000, 150, True), (11000, 600, 40, False), (64, 400, 4200, False),
+                                       (128, 600, 4200, False)])
+def test_rows_do_not_depend_on_the_call(env, oracle, L, K, n, mpv):
+    torch, rk = env
+    ks = rk.generate_kernels(900 + L, K, L)
+    rng = np.random.default_rng(L + K)
+    X = rng.standard_normal((n, L)).cumsum(1).astype(np.float32)
+    X /= np.abs(X).max(1, keepdims=True)
+    plan = rk.Plan(ks, L, mpv=mpv)
+    _log("rows of calls of any size L=%d K=%d n=%d mpv=%s" % (L, K, n, mpv))
+    Xd = torch.from_numpy(X).cuda()
+    F = plan.transform(Xd)
+    for lo, hi in ((0, 1), (1, 4), (5, 22), (n - 3, n)):
+        assert torch.equal(plan.transform(Xd[lo:hi].contiguous()), F[lo:hi]), (lo, hi)
+    rows = [0, n // 2, n - 1]
+    _check(F[rows].cpu().numpy(), oracle.transform(X[rows], ks), mpv, "rows of a long call")
