@@ -24,6 +24,7 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 PEAK_FP32_TFLOPS = 157.3      # MI355X dense fp32 (matrix and vector, published)
+PEAK_BF16_TFLOPS = 2500.0   # dense
 PEAK_FP32_FMA_NOPACK = 78.6   # fp32 vector FMA without packed instructions
 F_RESIDENT_LIMIT = 16 << 30   # above this the feature matrix is streamed in row batches
 DEFAULT_BATCH_ROWS = 100000
@@ -302,9 +303,10 @@ def main():
     # the layout the timed calls ran: series-lane for short univariate series
     # in calls of at least 4,096 series (then a permutation kernel writes F)
     series_path = bool(info.get("series_lane")) and batch >= 4096
-    # univariate workloads: kernel sets this large run split items, whose
-    # instructions the plan's fp32 counts do not describe
-    split = w.channels == 1 and not info["direct"]
+    # split items: dot products as six bf16 part products each, bounded by the
+    # bf16 matrix rate; the plan's fp32 counts describe the kernels they leave
+    split = info["split_items"] > 0 and not info["direct"]
+    peak = PEAK_BF16_TFLOPS / 6 if split else PEAK_FP32_TFLOPS
     kernel = ("rocket_split_series_kernel" if split else "rocket_series_kernel") if series_path else (
         "rocket_split_kernel" if split else "rocket_fused_kernel")
     traffic = None if (args.direct or args.mpv) else traffic_from_profile(w.name, digest, kernel)
@@ -368,7 +370,10 @@ def main():
     if split:
         path += "-split"
     kernel_name = ("rocket_direct_kernel" if info["direct"] else
-                   kernel + (" + rocket_slot_permute_kernel" if series_path else ""))
+                   kernel + (" + rocket_slot_permute_kernel" if series_path else "") +
+                   (" + fp32 items of %d kernels" % (w.n_kernels - info["split_kernels"])
+                    if split and info["split_kernels"] < w.n_kernels else "") +
+                   (" + rocket_toeplitz_kernel" if info["toeplitz_items"] and not series_path else ""))
     out = {
         "metric": "series*kernels/s (ROCKET transform, fp32, 1 MI355X)",
         "value": pairs_per_s,
@@ -388,8 +393,8 @@ def main():
                    "path": path},
         "pct_fp32_peak": 100.0 * achieved / PEAK_FP32_TFLOPS,
         "pct_fp32_fma_nopack_peak": 100.0 * achieved / PEAK_FP32_FMA_NOPACK,
-        "roofline": {"bound": "mfma", "achieved": achieved, "peak": PEAK_FP32_TFLOPS,
-                     "unit": "TFLOP/s", "frac": achieved / PEAK_FP32_TFLOPS, "traffic": traffic,
+        "roofline": {"bound": "bf16 mfma, six part products" if split else "mfma", "achieved": achieved,
+                     "peak": peak, "unit": "TFLOP/s", "frac": achieved / peak, "traffic": traffic,
                      "kernel": kernel_name,
                      "launches_per_step": launches, "launch_ms": per_launch_ms,
                      "algorithmic_flops_per_launch": flops_per_pass / launches,

@@ -178,9 +178,10 @@ rocket_status rocket_plan_create(const rocket_kernels *k, int32_t L, rocket_plan
  * 512 zeros on each side, and the series offset of each block of tiles
  * clamped into those margins on the scalar unit (same results).
  * Short univariate series (L <= 128): calls with at least 4,096 series run
- * by default in the series-lane layout.  The 64 lanes of a wavefront take 64
- * series, staged position-major in LDS, so every MFMA computes one output
- * position for 4 kernels x 64 series and each lane reduces its own series;
+ * by default in the series-lane layout.  The lanes of a wavefront take
+ * series (64, staged position-major in LDS), so every MFMA computes one output
+ * position for 4 kernels x 64 series (split items: 32 kernels x 32 series) and
+ * each lane reduces its own series;
  * the features go through a plan-owned buffer in slot order (allocated on
  * first use, at most 1 GiB, freed with the plan) and a permutation kernel
  * writes F; it runs on a stream the plan owns (non-blocking, default
@@ -220,9 +221,17 @@ void rocket_plan_destroy(rocket_plan *p);
  * passed (row batching is the caller's loop over pointer offsets).
  * X must be finite (see the rules at the top of this file).
  * Work may run on streams the plan owns (the Toeplitz items' kernel of a
- * plan that has them, the series-lane chunks); it starts after the work
+ * plan that has them, the fp32 items beside split items in long calls, the
+ * series-lane chunks); it starts after the work
  * queued on hip_stream before the call, and hip_stream waits for all of it,
  * so the call behaves as one stream-ordered operation on hip_stream.
+ * Features do not depend on n or on the batch a row is in.  The rounding of a
+ * kernel's dot products can depend on the other kernels of its set (whether
+ * it runs in a split item, and in which), not on their order: a subset of a
+ * set may give other last bits, and with them another count where a dot
+ * product is within rounding of zero.
+ * Dot products, their products and partial sums must stay within the fp32
+ * range (as must x, see the top); beyond it the features are unspecified.
  * A call that runs the series-lane layout (short series, n >= 4,096 or
  * ROCKET_PLAN_SERIES) allocates the plan's feature buffer on first use, or
  * grows it (hipMalloc, at most 1 GiB; growing first waits for the device),
@@ -296,9 +305,11 @@ rocket_status rocket_transform_host(const rocket_plan *p, const float *X_host, i
 
 /*
  * Plan facts for benchmarks and tests (host only).
- *   n_items      number of work items (groups of kernels sharing one bucket)
+ *   n_items      number of work items that run: groups of kernels sharing one
+ *                bucket, and split items (see rocket_plan_split_counts)
  *   n_buckets    number of distinct (length, dilation, padding) buckets
- *   mfma_per_row MFMA instructions one series costs (4x4x1 fp32 blocks;
+ *   mfma_per_row MFMA instructions one series costs in fp32 items (4x4x1 fp32
+ *                blocks; split items not counted;
  *                in the series-lane layout one MFMA serves 64 series, and
  *                this is the rounded share of one series)
  *   lds_bytes    LDS one workgroup uses (0 for the direct kernel)
@@ -323,8 +334,8 @@ rocket_status rocket_transform_host(const rocket_plan *p, const float *X_host, i
  *                run without MFMA
  *   toeplitz_items  work items of the shifted-kernel (Toeplitz) form: the
  *                one or two kernels left over in a bucket at a large
- *                dilation, run in a second kernel launch of each call
- *                (0: one launch per call)
+ *                dilation, run in a kernel launch of their own beside the
+ *                others of each call
  */
 typedef struct {
     int64_t n_items;
@@ -345,6 +356,21 @@ typedef struct {
 /* Fill *out with the plan's facts.  Errors: ROCKET_ERR_INVALID_ARG if p or
  * out is NULL. */
 rocket_status rocket_plan_info(const rocket_plan *p, rocket_plan_facts *out);
+
+/*
+ * Split items of a plan (0 and 0 where it has none).  Univariate sets run
+ * most kernels as split items where that is faster: groups of up to 32 kernels
+ * of one dilation, every fp32 weight and sample as the exact sum of three bf16
+ * parts, the six largest part products summed in fp32 by bf16 MFMA.  Weights
+ * outside 2^-64 .. 2^64 (but 0), dilations above 65,536, kernels of more than
+ * 65,535 outputs, multivariate sets, series of more than about 20,280 samples,
+ * kernels with a bias below 2^-100 of their weights' sum, and small sets run
+ * fp32 items.
+ *   items    number of split items
+ *   kernels  kernels they hold; the others run in the plan's fp32 items
+ * Errors: ROCKET_ERR_INVALID_ARG for a NULL argument.
+ */
+rocket_status rocket_plan_split_counts(const rocket_plan *p, int64_t *items, int64_t *kernels);
 
 /*
  * Host-side work tables of the fused kernel, for tests and tools (no GPU is

@@ -389,6 +389,10 @@ rocket_status build_split_plan(const rocket_kernels *k, int32_t L, SplitPlan *ou
         for (int32_t i = 0; i < k->n_kernels; ++i)
             (bias_carries(k, i) ? by_dil : fp32_only)[{k->dilation[i], k->length[i] % 2 == 0}].push_back(
                 Row{i, ell_index_for(k->length[i]), outputs(k, i, L)});
+        std::vector<std::array<int64_t, 3>> bucket;
+        for (int32_t i = 0; i < k->n_kernels; ++i) bucket.push_back({k->dilation[i], k->length[i], k->padding[i]});
+        std::sort(bucket.begin(), bucket.end());
+        P.n_buckets = std::unique(bucket.begin(), bucket.end()) - bucket.begin();
         // by their own numbers (a total order but for equal kernels), so that a
         // kernel's item, and with it the rounding of its dot products, does not
         // depend on the set's order

@@ -237,6 +237,7 @@ struct SplitPlan {
     std::vector<int32_t> split_begin;
     std::vector<int32_t> layout_off;
     std::vector<int32_t> rest;    // kernels left to the fp32 items (ascending)
+    int64_t n_buckets = 0;        // distinct (length, dilation, padding) of the set
     double cost = 0.0;            // issue cycles per series of the items
     double rest_cost = 0.0;       // and of the rest as fp32 items
     double fp32_cost = 0.0;       // and of all kernels as fp32 items

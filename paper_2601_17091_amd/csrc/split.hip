@@ -881,6 +881,9 @@ rocket_status split_launch_series(const SplitDevice *d, const float *X, int64_t 
 int64_t split_lds_bytes(const SplitDevice *d) { return d->lds; }
 double split_rest_cost(const SplitDevice *d) { return d->host.rest_cost; }
 int split_rows_per_block(const SplitDevice *d) { return d->rows; }
+int64_t split_n_items(const SplitDevice *d) { return (int64_t)d->host.items.size(); }
+int64_t split_n_rest(const SplitDevice *d) { return (int64_t)d->host.rest.size(); }
+int64_t split_n_buckets(const SplitDevice *d) { return d->host.n_buckets; }
 bool split_one_per_cu(const SplitDevice *d) { return d->shape == 2; }
 
 hipError_t split_create(SplitPlan &&plan, int device, int n_cu, int64_t lds_limit, bool mpv, SplitDevice **out) {

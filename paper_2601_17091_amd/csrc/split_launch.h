@@ -22,6 +22,10 @@ rocket_status split_launch_series(const SplitDevice *d, const float *X, int64_t 
                                   hipStream_t s);
 int64_t split_lds_bytes(const SplitDevice *d);
 int split_rows_per_block(const SplitDevice *d);
+// Items; kernels left to fp32 items; distinct (length, dilation, padding) of the set.
+int64_t split_n_items(const SplitDevice *d);
+int64_t split_n_rest(const SplitDevice *d);
+int64_t split_n_buckets(const SplitDevice *d);
 // Rows above 40 KB: one workgroup per CU.
 bool split_one_per_cu(const SplitDevice *d);
 // Issue cycles per series of the kernels left to fp32 items.

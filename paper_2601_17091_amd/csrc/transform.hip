@@ -738,16 +738,12 @@ static const void *series_fn(bool mpv) {
 
 struct rocket_plan {
     rocket::HostPlan host;  // fp32 items: of every kernel, or of those split items leave over
-    // split items (univariate plans of series longer than kSeriesMaxL): most
-    // kernels run there, the rest in fp32 items of the same launch (Toeplitz
-    // items in their own)
+    // split items (univariate plans, see split_eligible and split_pays): most
+    // kernels run there, for series longer than kSeriesMaxL the rest in fp32
+    // items of the same launch or one beside it (Toeplitz items in their own)
     rocket::SplitDevice *split = nullptr;
     bool split_rest = false;  // some kernels are left to fp32 items
     int64_t fp32_slots = 0;   // slots of the fp32 items of the whole set (0: few)
-    // a split plan's kernel set (host), for the facts of rocket_plan_info,
-    // which describe the fp32 items of the whole set
-    std::vector<int32_t> k_len, k_dil, k_pad;
-    std::vector<float> k_bias, k_w;
     // code variants in launch order: by total item cost, largest first
     int32_t variant_order[rocket::kNumVariants] = {};
     int device = 0;
@@ -1029,15 +1025,6 @@ extern "C" rocket_status rocket_plan_create_ex(const rocket_kernels *k, int32_t 
                 st = rocket::build_host_plan(k, L, &whole);
                 p->fp32_slots = (int64_t)whole.kid.size();
             }
-            try {
-                p->k_len.assign(k->length, k->length + k->n_kernels);
-                p->k_dil.assign(k->dilation, k->dilation + k->n_kernels);
-                p->k_pad.assign(k->padding, k->padding + k->n_kernels);
-                p->k_bias.assign(k->bias, k->bias + k->n_kernels);
-                p->k_w.assign(k->weights, k->weights + (int64_t)k->n_kernels * k->max_len);
-            } catch (const std::bad_alloc &) {
-                st = ROCKET_ERR_OOM;
-            }
             if (st == ROCKET_OK)
                 e = rocket::split_create(std::move(sp), p->device, p->n_cu, (int64_t)prop.sharedMemPerBlock, p->mpv,
                                      &p->split);
@@ -1176,24 +1163,16 @@ extern "C" rocket_status rocket_check_flags(uint32_t *flags) {
 extern "C" rocket_status rocket_plan_info(const rocket_plan *p, rocket_plan_facts *out) {
     if (!p || !out) return ROCKET_ERR_INVALID_ARG;
     std::memset(out, 0, sizeof(*out));
+    item_facts(p->host, p->series, p->minirocket, out);
     if (p->split) {
-        rocket_kernels k;
-        std::memset(&k, 0, sizeof(k));
-        k.n_kernels = p->host.n_kernels;
-        k.max_len = p->max_len;
-        k.length = const_cast<int32_t *>(p->k_len.data());
-        k.dilation = const_cast<int32_t *>(p->k_dil.data());
-        k.padding = const_cast<int32_t *>(p->k_pad.data());
-        k.bias = const_cast<float *>(p->k_bias.data());
-        k.weights = const_cast<float *>(p->k_w.data());
-        rocket::HostPlan whole;
-        const rocket_status st = rocket::build_host_plan(&k, p->host.L, &whole);
-        if (st != ROCKET_OK) return st;
-        item_facts(whole, p->series, false, out);
-    } else {
-        item_facts(p->host, p->series, p->minirocket, out);
+        // the plan's fp32 items are what split items leave over
+        out->n_items += rocket::split_n_items(p->split);
+        out->n_buckets = rocket::split_n_buckets(p->split);
     }
-    out->lds_bytes = p->series ? (p->split ? rocket::split_series_lds(p->host.L) : p->series_lds) : (p->split ? rocket::split_lds_bytes(p->split) : p->lds_bytes);
+    if (p->split)
+        out->lds_bytes = p->series ? rocket::split_series_lds(p->host.L) : rocket::split_lds_bytes(p->split);
+    else
+        out->lds_bytes = p->series ? p->series_lds : p->lds_bytes;
     out->direct = p->direct ? 1 : 0;
     out->clamped = p->clamp ? 1 : 0;
     out->features_per_kernel = p->minirocket ? 0 : (p->mpv ? 3 : 2);
@@ -1204,6 +1183,16 @@ extern "C" rocket_status rocket_plan_info(const rocket_plan *p, rocket_plan_fact
                           : p->series ? kSeriesLanes
                           : p->split  ? rocket::split_rows_per_block(p->split)
                                       : p->rows_per_block;
+    return ROCKET_OK;
+}
+
+extern "C" rocket_status rocket_plan_split_counts(const rocket_plan *p, int64_t *items, int64_t *kernels) {
+    if (!p || !items || !kernels) return ROCKET_ERR_INVALID_ARG;
+    *items = *kernels = 0;
+    if (p->split) {
+        *items = rocket::split_n_items(p->split);
+        *kernels = p->host.n_kernels - rocket::split_n_rest(p->split);
+    }
     return ROCKET_OK;
 }
 

@@ -48,6 +48,7 @@ EXPORTED = (
     "rocket_transform",
     "rocket_transform_host",
     "rocket_plan_info",
+    "rocket_plan_split_counts",
     "rocket_plan_tables_build",
     "rocket_plan_tables_free",
     "rocket_status_string",
@@ -140,6 +141,7 @@ def _signatures() -> dict:
         "rocket_transform": ([vp, i64, i32, kp, vp, vp], st),
         "rocket_transform_host": ([vp, vp, i64, vp, i64, vp], st),
         "rocket_plan_info": ([vp, ctypes.POINTER(CPlanFacts)], st),
+        "rocket_plan_split_counts": ([vp, ctypes.POINTER(i64), ctypes.POINTER(i64)], st),
         "rocket_plan_tables_build": ([kp, i32, ctypes.POINTER(CPlanTables)], st),
         "rocket_plan_tables_free": ([ctypes.POINTER(CPlanTables)], None),
         "rocket_status_string": ([ctypes.c_int], ctypes.c_char_p),
@@ -385,12 +387,15 @@ class Plan:
     def info(self) -> dict:
         f = CPlanFacts()
         _check(self._lib.rocket_plan_info(self._h, ctypes.byref(f)), "rocket_plan_info")
+        items, kernels = ctypes.c_int64(), ctypes.c_int64()
+        _check(self._lib.rocket_plan_split_counts(self._h, ctypes.byref(items), ctypes.byref(kernels)),
+               "rocket_plan_split_counts")
         return dict(n_items=f.n_items, n_buckets=f.n_buckets, mfma_per_row=f.mfma_per_row,
                     lds_bytes=f.lds_bytes, direct=bool(f.direct), clamped=bool(f.clamped),
                     features_per_kernel=f.features_per_kernel, rows_per_block=f.rows_per_block,
                     n_features=f.n_features, minirocket=bool(f.minirocket),
                     series_lane=bool(f.series_lane), valu_fma_per_row=f.valu_fma_per_row,
-                    toeplitz_items=f.toeplitz_items)
+                    toeplitz_items=f.toeplitz_items, split_items=items.value, split_kernels=kernels.value)
 
     @property
     def n_features(self) -> int:
