@@ -254,3 +254,36 @@ def assert_mpv_parity(F3, ref, what=""):
     assert np.all(err <= lim), (what, float((err - lim).max()))
     r["mpv_max_rel_err"] = float((err / np.maximum(np.abs(ref["mpv"][same]), 1e-30)).max()) if err.size else 0.0
     return r
+
+
+def many_widths_set(L, seed, dilations=(1, 2, 3, 12, 13), each=3):
+    """Kernels of every length from 1 to 11 at each dilation, with paddings
+    that give one of four numbers of outputs (the same for every length of one
+    parity of (length - 1) d), so that groups of up to 32 of them hold several
+    lengths and widths; and 40 kernels of length 11 at the largest dilation."""
+    rng = np.random.default_rng(seed)
+    ln, dil, pad = [], [], []
+    for d in dilations:
+        for length in range(1, 12):
+            span = (length - 1) * d
+            for extra in (0, 10, 22, 40):
+                extra += span % 2
+                if L + extra < 1 or span + extra < 0:
+                    continue
+                ln += [length] * each
+                dil += [d] * each
+                pad += [(span + extra) // 2] * each      # O = L + extra
+    ln += [11] * 40
+    dil += [(L - 1) // 10] * 40
+    pad += [0] * 40                                       # O = L - 10 d
+    return kernel_set(ln, dil, pad, rng.uniform(-1, 1, len(ln)), [rng.standard_normal(n) for n in ln])
+
+
+def full_dilations_set(L, count, seed, dilations=range(1, 13)):
+    """`count` kernels of lengths 7, 9 and 11 at each dilation, half of them
+    centred."""
+    rng = np.random.default_rng(seed)
+    ln = [7, 9, 11] * (count * len(dilations))
+    dil = [d for d in dilations for _ in range(3 * count)]
+    pad = [(n - 1) * d // 2 if rng.integers(2) else 0 for n, d in zip(ln, dil)]
+    return kernel_set(ln, dil, pad, rng.uniform(-1, 1, len(ln)), [rng.standard_normal(n) for n in ln])

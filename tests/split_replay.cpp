@@ -3,6 +3,7 @@
 #include <cmath>
 #include <cstring>
 #include <limits>
+#include <set>
 #include <vector>
 
 #include "rocket_internal.h"
@@ -26,10 +27,12 @@ static double dot2(uint32_t a, uint32_t b) {
 
 // 0: everything agrees; otherwise the number of the check that failed, with
 // the kernel in *where.  series: the series-lane layout's blocks and margins.
+// *forms: bit 0 an item of three or more widths, bit 1 of several lengths, bit
+// 2 of even lengths, bit 3 with a kernel of at most two outputs.
 extern "C" int split_replay(const rocket_kernels *k, int32_t L, const float *x, int32_t series, int32_t *where,
-                            int32_t *n_items) {
+                            int32_t *n_items, int32_t *forms) {
     *where = -1;
-    *n_items = 0;
+    *n_items = *forms = 0;
     if (!split_eligible(k, L)) return 1;
     SplitPlan P;
     if (build_split_plan(k, L, &P) != ROCKET_OK) return 2;
@@ -62,6 +65,15 @@ extern "C" int split_replay(const rocket_kernels *k, int32_t L, const float *x, 
     }
     const int tile = series ? 1 : kSplitTile, block = 2 * tile, margin = series ? kSplitSeriesMargin : kSplitMargin;
     for (const SplitItem &it : P.items) {
+        std::set<int64_t> widths, lengths;
+        for (int q = 0; q < it.n_rows; ++q) {
+            const int32_t kk = P.kid[it.r_off + q], len = k->length[kk];
+            const int64_t O = (int64_t)L + 2 * (int64_t)k->padding[kk] - (int64_t)(len - 1) * k->dilation[kk];
+            widths.insert(O);
+            lengths.insert(len);
+            *forms |= (len % 2 == 0 ? 4 : 0) | (O <= 2 ? 8 : 0);
+        }
+        *forms |= (widths.size() >= 3 ? 1 : 0) | (lengths.size() >= 2 ? 2 : 0);
         const int v = it.variant, nf = kSplitFrags[v];
         const int lo = series ? it.series_lo : it.clean_lo, hi = series ? it.series_hi : it.clean_hi;
         const int n_blocks = (it.n_cols + block - 1) / block;

@@ -1,15 +1,15 @@
-"""Split items (fp32 dot products as bf16 part products, series longer than
-128 samples) where they can go wrong: the shortest and longest rows they take,
-lengths that leave one column in the last tile or block, 1 to 33 kernels of a
-dilation, every kernel length with paddings that are not centred, rows of many
-widths in one item, series scaled to the ends of the fp32 range, and rows
-beside a row of NaN and infinities."""
+"""Split items (fp32 dot products as bf16 part products) where they can go
+wrong, in the tiled and the series-lane layout: the shortest and longest rows
+they take, lengths that leave one column in the last tile or block, 1 to 65
+kernels of a dilation, every kernel length, kernels of many widths in one item,
+exact sums, series scaled to the ends of the fp32 range, rows beside a row of
+NaN and infinities, calls of all sizes and captured calls."""
 import sys
 
 import numpy as np
 import pytest
 
-from _util import assert_mpv_parity, assert_parity, kernel_set
+from _util import assert_mpv_parity, assert_parity, full_dilations_set, kernel_set, many_widths_set
 
 pytestmark = pytest.mark.gpu
 
@@ -29,9 +29,13 @@ def env():
     return torch, rk
 
 
-def _run(env, ks, X, **kw):
+def _run(env, ks, X, split=True, **kw):
+    """Features of X; split: whether the plan has to have split items (None:
+    either)."""
     torch, rk = env
-    F = rk.Plan(ks, X.shape[1], **kw).transform(torch.from_numpy(X).cuda())
+    plan = rk.Plan(ks, X.shape[1], **kw)
+    assert split is None or (plan.info()["split_items"] > 0) == split
+    F = plan.transform(torch.from_numpy(X).cuda())
     torch.cuda.synchronize()
     return F.cpu().numpy()
 
@@ -47,7 +51,7 @@ def _check(F, ref, mpv, what):
 @pytest.mark.parametrize("L", [129, 193, 257, 1021, 3200, 6463, 6464, 6465, 9983, 9984, 9985, 20255, 20300])
 def test_row_lengths(env, oracle, L):
     _, rk = env
-    K = 400 if L < 4000 else 1000   # enough that items of 32 pay at this length
+    K = 2500 if L < 4000 else 4000   # enough that split items pay at this length
     ks = rk.generate_kernels(3000 + L, K, L)
     rng = np.random.default_rng(L)
     X = rng.standard_normal((5 if L < 4000 else 2, L)).cumsum(1)
@@ -55,51 +59,47 @@ def test_row_lengths(env, oracle, L):
     ref = oracle.transform(X, ks)
     for mpv in (False, True):
         _log("L=%d mpv=%s" % (L, mpv))
-        _check(_run(env, ks, X, mpv=mpv), ref, mpv, "L=%d" % L)
+        _check(_run(env, ks, X, split=L < 20300, mpv=mpv), ref, mpv, "L=%d" % L)
 
 
-@pytest.mark.parametrize("clamped", [False, True])
-@pytest.mark.parametrize("L", [131, 320])
-def test_lengths_and_paddings(env, oracle, L, clamped):
-    """Every length from 1 to 11 with paddings 0 .. 40, so that one dilation
-    holds rows of many widths (an item masks two or four) and of both length
-    parities; dilations up to O = 1."""
-    rng = np.random.default_rng(17 + L)
-    ln, dil, pad, w = [], [], [], []
-    for d in (1, 2, 3, 12, 13, 26):
-        for length in range(1, 12):
-            for p in rng.integers(0, 41, 1 + (d * length) % 5):
-                if L + 2 * p - (length - 1) * d < 1:
-                    p = ((length - 1) * d) // 2
-                ln.append(length)
-                dil.append(d)
-                pad.append(int(p))
-                w.append(rng.standard_normal(length))
-    for length, d in ((11, (L - 1) // 10), (9, (L - 1) // 8), (7, (L - 1) // 6)):
-        ln += [length] * 3
-        dil += [d] * 3
-        pad += [0] * 3
-        w += [rng.standard_normal(length) for _ in range(3)]
-    ks = kernel_set(ln, dil, pad, rng.uniform(-1, 1, len(ln)), w)
-    X = rng.standard_normal((4, L)).astype(np.float32)
-    _log("lengths and paddings L=%d clamped=%s, %d kernels" % (L, clamped, len(ln)))
+@pytest.mark.parametrize("L,kw", [(41, {}), (41, dict(series=True)), (131, {}), (321, {}), (321, dict(clamped=True))])
+def test_lengths_and_paddings(env, oracle, L, kw):
+    """Items of several lengths, even ones among them, of three and four
+    widths (an item masks two or four), and of kernels with one output."""
+    ks = many_widths_set(L, L)
+    X = np.random.default_rng(17 + L).standard_normal((4, L)).astype(np.float32)
+    _log("lengths and paddings L=%d %s, %d kernels" % (L, kw, len(ks["length"])))
     ref = oracle.transform(X, ks)
     for mpv in (False, True):
-        _check(_run(env, ks, X, mpv=mpv, clamped=clamped), ref, mpv, "paddings")
+        _check(_run(env, ks, X, mpv=mpv, **kw), ref, mpv, "paddings")
+
+
+@pytest.mark.parametrize("L", [41, 321])
+def test_exact_sums(env, oracle, L):
+    """Integer series, weights and biases: every partial sum is exact, so PPV
+    and MAX equal the oracle's, with many sums that cancel to zero."""
+    ks = many_widths_set(L, L)
+    rng = np.random.default_rng(L)
+    ks["weights"] = np.where(ks["weights"] != 0, rng.integers(-2, 3, ks["weights"].shape), 0).astype(np.float32)
+    ks["bias"] = rng.choice([-2, -1, 1, 2], len(ks["bias"])).astype(np.float32)
+    X = rng.integers(-3, 4, (5, L)).astype(np.float32)
+    X[1], X[2], X[3] = 0.0, np.float32(-0.0), 1.5
+    _log("exact sums L=%d" % L)
+    ref = oracle.transform(X, ks)
+    for kw in ([dict(series=True), {}] if L <= 128 else [{}]):
+        F = _run(env, ks, X, **kw)
+        np.testing.assert_array_equal(F[:, 0::2], ref["cnt"].astype(np.float32) / ref["O"][None].astype(np.float32))
+        np.testing.assert_array_equal(F[:, 1::2], ref["F"][:, 1::2])
 
 
 @pytest.mark.parametrize("count", [1, 2, 15, 31, 32, 33, 65])
 def test_kernels_per_dilation(env, oracle, count):
-    """A dilation's kernels fill one item, one less, one more, and two."""
-    rng = np.random.default_rng(count)
-    L = 400
-    ln = [7, 9, 11] * count
-    dil = [2] * (3 * count)
-    pad = [(l - 1) if rng.integers(2) else 0 for l in ln]
-    ks = kernel_set(ln, dil, pad, rng.uniform(-1, 1, len(ln)), [rng.standard_normal(l) for l in ln])
-    X = rng.standard_normal((3, L)).astype(np.float32)
-    _log("%d kernels of each length at one dilation" % count)
-    _check(_run(env, ks, X), oracle.transform(X, ks), False, "count=%d" % count)
+    """A dilation's kernels fill one item, one less, one more, and two (a
+    handful is left to fp32 items)."""
+    ks = full_dilations_set(400, count, count)
+    X = np.random.default_rng(count).standard_normal((3, 400)).astype(np.float32)
+    _log("%d kernels of each length at a dilation" % count)
+    _check(_run(env, ks, X, split=count >= 15), oracle.transform(X, ks), False, "count=%d" % count)
 
 
 @pytest.mark.parametrize("e", [-80, -40, 40, 110])
@@ -108,7 +108,7 @@ def test_power_of_two_scaling(env, e):
     and sum exactly (all parts stay normal at 2^-80): PPV is unchanged and
     MAX scales bit for bit, up to sums near the fp32 maximum."""
     _, rk = env
-    ks = rk.generate_kernels(77, 500, 300)
+    ks = rk.generate_kernels(77, 1500, 300)
     rng = np.random.default_rng(5)
     X = rng.standard_normal((3, 300)).astype(np.float32)
     a = _run(env, ks, X)
@@ -124,7 +124,7 @@ def test_neighbour_rows_do_not_mix(env):
     beside them as they are alone."""
     torch, rk = env
     for L in (150, 500):
-        ks = rk.generate_kernels(78, 600, L)
+        ks = rk.generate_kernels(78, 1500, L)
         rng = np.random.default_rng(6)
         X = rng.standard_normal((7, L)).astype(np.float32)
         want = _run(env, ks, X)
@@ -147,6 +147,9 @@ def test_captured_call(env, L, bias):
     if not bias:
         ks["bias"][:] = 0.0
     plan = rk.Plan(ks, L, clamped=True)
+    info = plan.info()
+    assert (info["split_items"] > 0) == bias
+    assert info["toeplitz_items"] > 0 or L == 500
     X = torch.randn((6, L), device="cuda")
     want = plan.transform(X)
     F, F2 = torch.zeros_like(want), torch.zeros_like(want)
@@ -198,7 +201,7 @@ def test_far_taps(env, oracle, L, d, kw):
     ks = kernel_set([3] * n, [d] * n, [d] * n, rng.uniform(-1, 1, n), [rng.standard_normal(3) for _ in range(n)])
     X = rng.standard_normal((70, L)).astype(np.float32)
     _log("far taps L=%d d=%d %s" % (L, d, kw))
-    _check(_run(env, ks, X, **kw), oracle.transform(X, ks), False, "far taps")
+    _check(_run(env, ks, X, split=None, **kw), oracle.transform(X, ks), False, "far taps")
 
 
 @pytest.mark.parametrize("L,kw", [(100, dict(series=True)), (100, dict(tiled=True)), (400, {})])
@@ -214,7 +217,7 @@ def test_tiny_samples(env, L, kw):
     rng = np.random.default_rng(83)
     X = rng.standard_normal((4, L)).astype(np.float32)
     _log("tiny samples L=%d %s" % (L, kw))
-    a, b = _run(env, ks, X, **kw), _run(env, ks, np.ldexp(X, -120).astype(np.float32), **kw)
+    a, b = (_run(env, ks, Y, split=False, **kw) for Y in (X, np.ldexp(X, -120).astype(np.float32)))
     back = np.ldexp(b[:, 1::2].astype(np.float64), 120)
     np.testing.assert_allclose(back, a[:, 1::2], rtol=0, atol=11 * 2.0 ** -20)
 
@@ -233,6 +236,7 @@ def test_rows_do_not_depend_on_the_call(env, oracle, L, K, n, mpv):
     X = rng.standard_normal((n, L)).cumsum(1).astype(np.float32)
     X /= np.abs(X).max(1, keepdims=True)
     plan = rk.Plan(ks, L, mpv=mpv)
+    assert plan.info()["split_items"] > 0
     _log("rows of calls of any size L=%d K=%d n=%d mpv=%s" % (L, K, n, mpv))
     Xd = torch.from_numpy(X).cuda()
     F = plan.transform(Xd)

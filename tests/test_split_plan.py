@@ -13,7 +13,7 @@ import pytest
 
 import paper_2601_17091_amd as rk
 from paper_2601_17091_amd import rocket
-from _util import kernel_set
+from _util import full_dilations_set, kernel_set, many_widths_set
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -37,16 +37,16 @@ def replay_lib(tmp_path_factory):
 def replay(replay_lib):
     lib = replay_lib
 
-    def run(ks, L, series, seed=0, may_refuse=False):
+    def run(ks, L, series, seed=0, may_refuse=False, with_forms=False):
         x = np.random.default_rng(seed).standard_normal(L).astype(np.float32)
         c, keep = rocket.as_c_kernels(ks)
-        where, items = ctypes.c_int32(), ctypes.c_int32()
+        where, items, forms = ctypes.c_int32(), ctypes.c_int32(), ctypes.c_int32()
         rc = lib.split_replay(ctypes.byref(c), L, x.ctypes.data_as(ctypes.POINTER(ctypes.c_float)), int(series),
-                              ctypes.byref(where), ctypes.byref(items))
+                              ctypes.byref(where), ctypes.byref(items), ctypes.byref(forms))
         if may_refuse and rc == 1:
             return 0
         assert rc == 0, "check %d failed at kernel %d" % (rc, where.value)
-        return items.value
+        return (items.value, forms.value) if with_forms else items.value
 
     return run
 
@@ -63,33 +63,22 @@ def test_generated(replay, L):
     assert replay(rk.generate_kernels(3000 + L, 400 if L < 4000 else 1500, L), L, False) > 0
 
 
-@pytest.mark.parametrize("L", [40, 131, 320])
+@pytest.mark.parametrize("L", [41, 131, 321])
 def test_lengths_and_paddings(replay, L):
-    rng = np.random.default_rng(L)
-    ln, dil, pad, w = [], [], [], []
-    for d in (1, 2, 3, 12, 13, 26, 39):
-        for length in range(1, 12):
-            for p in rng.integers(0, 41, 1 + (d * length) % 6):
-                if L + 2 * p - (length - 1) * d < 1:
-                    p = (length - 1) * d - L // 2       # O of 1 or 2 and up
-                    p = (p + 1) if L + 2 * p - (length - 1) * d >= 1 else ((length - 1) * d) // 2
-                ln.append(length)
-                dil.append(d)
-                pad.append(int(max(p, 0)))
-                w.append(rng.standard_normal(length))
-    ks = kernel_set(ln, dil, pad, rng.uniform(-1, 1, len(ln)), w)
+    """Items of several lengths, even ones among them, of three and four
+    widths, and of kernels with one output."""
+    ks = many_widths_set(L, L)
     for series in ((False, True) if L <= 128 else (False,)):
-        replay(ks, L, series)
+        items, forms = replay(ks, L, series, with_forms=True)
+        assert items > 0 and forms == 15
 
 
 @pytest.mark.parametrize("count", [1, 2, 15, 31, 32, 33, 65])
 def test_kernels_per_dilation(replay, count):
-    rng = np.random.default_rng(count)
-    ln = [7, 9, 11] * count
-    pad = [(length - 1) if rng.integers(2) else 0 for length in ln]
-    ks = kernel_set(ln, [2] * len(ln), pad, rng.uniform(-1, 1, len(ln)), [rng.standard_normal(n) for n in ln])
-    for L in (100, 400):
-        replay(ks, L, L == 100)
+    for L, dilations in ((100, range(1, 9)), (400, range(1, 13))):
+        items = replay(full_dilations_set(L, count, count, dilations), L, L == 100)
+        # a handful of kernels a dilation is left to fp32 items
+        assert items >= 2 * len(dilations) * (3 * count // 64) and (items > 0) == (count >= 15)
 
 
 @pytest.mark.parametrize("L,d,series", [(100, 1 << 16, True), (100, 1 << 22, True), (128, 1 << 24, True),
