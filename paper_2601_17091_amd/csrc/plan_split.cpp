@@ -5,7 +5,6 @@
 #include <array>
 #include <cmath>
 #include <cstring>
-#include <map>
 #include <new>
 #include <utility>
 #include <vector>
@@ -88,8 +87,9 @@ namespace {
 
 struct Row {
     int32_t k;
-    int v;  // variant of its own length
-    int64_t O;
+    int32_t v;  // variant of its own length
+    int32_t O;  // at most kSplitMaxOutputs
+    float bias;
 };
 
 struct Group {
@@ -122,9 +122,9 @@ void group_bounds(const Group &g, int32_t L, int32_t d, bool even, int32_t reach
 // (out null: only their cost).
 void cut(const Row *rows, size_t n, int32_t L, int32_t d, bool even, std::vector<Group> *out, double &cost) {
     Group g;
-    size_t n_slots = 0;
-    auto flush = [&]() {
-        if (n_slots == 0) return;
+    size_t first = 0;  // the group's rows are first .. i - 1
+    auto flush = [&](size_t end) {
+        if (first == end) return;
         int64_t s0, lo, hi;
         if (L <= kSeriesMaxL) {
             // series-lane: a tile is one position of 32 series
@@ -139,28 +139,32 @@ void cut(const Row *rows, size_t n, int32_t L, int32_t d, bool even, std::vector
                      kItemRowCycles;
         }
         cost += g.cost;
-        if (out) out->push_back(std::move(g));
-        g = Group();
-        n_slots = 0;
+        if (out) {
+            for (size_t i = first; i < end; ++i) g.slot.push_back(rows[i].k);
+            out->push_back(std::move(g));
+            g.slot = std::vector<int32_t>();
+        }
+        g.variant = g.n_widths = 0;
+        first = end;
     };
     for (size_t i = 0; i < n; ++i) {
         const Row &r = rows[i];
-        auto known = [&]() {
-            for (int w = 0; w < g.n_widths; ++w)
-                if (g.widths[w] == r.O) return true;
-            return false;
-        };
-        const int v = std::max(g.variant, r.v);
-        if (n_slots == (size_t)kSplitRows || (!known() && g.n_widths == kSplitWidths[v])) flush();
-        if (n_slots == 0) g.n_cols = g.o_min = r.O;
-        if (!known()) g.widths[g.n_widths++] = r.O;
-        if (out) g.slot.push_back(r.k);
-        ++n_slots;
+        // (rows of one width mostly follow each other)
+        int64_t *end = g.widths + g.n_widths;
+        bool known = g.n_widths > 0 && (end[-1] == r.O || std::find(g.widths, end, r.O) != end);
+        if (i - first == (size_t)kSplitRows || (!known && g.n_widths == kSplitWidths[std::max(g.variant, r.v)])) {
+            flush(i);
+            known = false;
+        }
+        if (first == i) g.n_cols = g.o_min = r.O;
+        if (!known) {
+            g.widths[g.n_widths++] = r.O;
+            g.n_cols = std::max<int64_t>(g.n_cols, r.O);
+            g.o_min = std::min<int64_t>(g.o_min, r.O);
+        }
         g.variant = std::max(g.variant, r.v);
-        g.n_cols = std::max(g.n_cols, r.O);
-        g.o_min = std::min(g.o_min, r.O);
     }
-    flush();
+    flush(n);
 }
 
 // The same of a group's kernels as fp32 items: 4-kernel MFMA groups and VALU
@@ -200,45 +204,51 @@ double fp32_cycles(const Group &g, const rocket_kernels *k, int64_t L) {
 // nearly the same O and run best with lengths apart; at large ones an item is
 // filled only by everything the dilation has.
 static std::vector<Group> best_groups(const std::vector<Row> &rows, int32_t L, int32_t d, bool even) {
-    // which variants run together: {7}{9}{11}, {7,9,11}, {7}{9,11}, {7,9}{11}
-    static const int kParts[4][kSplitVariants] = {{0, 1, 2}, {0, 0, 0}, {0, 1, 1}, {0, 0, 1}};
+    // which variants run together (bit masks): {7}{9}{11}, {7,9,11}, {7}{9,11}, {7,9}{11}
+    static const int kParts[4][kSplitVariants] = {{1, 2, 4}, {7, 0, 0}, {1, 6, 0}, {3, 4, 0}};
     // longest frame first, or widest first
+    if (rows.empty()) return {};
     std::vector<Row> order[2] = {rows, rows}, sel;
     std::stable_sort(order[0].begin(), order[0].end(),
                      [](const Row &a, const Row &b) { return a.v != b.v ? a.v > b.v : a.O > b.O; });
     std::stable_sort(order[1].begin(), order[1].end(),
                      [](const Row &a, const Row &b) { return a.O != b.O ? a.O > b.O : a.v > b.v; });
-    auto run = [&](int part, int how, std::vector<Group> *out) {
+    // how 2: widest first, a group boundary wherever O changes
+    auto run = [&](int mask, int how, std::vector<Group> *out) {
         double cost = 0.0;
-        for (int q = 0; q < kSplitVariants; ++q) {
-            const Row *r = order[how == 0 ? 0 : 1].data();
-            size_t n = rows.size();
-            if (part != 1) {
-                sel.clear();
-                for (size_t i = 0; i < rows.size(); ++i)
-                    if (kParts[part][r[i].v] == q) sel.push_back(r[i]);
-                r = sel.data();
-                n = sel.size();
-            } else if (q > 0) {
-                break;
-            }
-            // how 2: a group boundary wherever O changes
-            for (size_t i = 0; i < n;) {
-                size_t j = how == 2 ? i : n;
-                while (j < n && r[j].O == r[i].O) ++j;
-                cut(r + i, j - i, L, d, even, out, cost);
-                i = j;
-            }
+        const std::vector<Row> &all = order[how == 0 ? 0 : 1];
+        const Row *r = all.data();
+        size_t n = all.size();
+        if (mask != 7) {
+            sel.clear();
+            for (const Row &x : all)
+                if ((mask >> x.v) & 1) sel.push_back(x);
+            r = sel.data();
+            n = sel.size();
+        }
+        for (size_t i = 0; i < n;) {
+            size_t j = how == 2 ? i : n;
+            while (j < n && r[j].O == r[i].O) ++j;
+            cut(r + i, j - i, L, d, even, out, cost);
+            i = j;
         }
         return cost;
     };
     int best_part = 1, best_how = 0;
     // (a handful of kernels makes one group or none)
     if (rows.size() > 6) {
-        double best = -1.0;
+        double best = -1.0, known[3][8];
+        std::fill(&known[0][0], &known[0][0] + 24, -1.0);
         for (int part = 0; part < 4; ++part)
             for (int how = 0; how < 3; ++how) {
-                const double c = run(part, how, nullptr);
+                double c = 0.0;
+                for (int mask : kParts[part]) {
+                    if (mask == 0) continue;
+                    // one variant: both orders are the same
+                    double &k = known[how == 1 && (mask & (mask - 1)) == 0 ? 0 : how][mask];
+                    if (k < 0.0) k = run(mask, how, nullptr);
+                    c += k;
+                }
                 if (best < 0.0 || c < best) {
                     best = c;
                     best_part = part;
@@ -247,7 +257,8 @@ static std::vector<Group> best_groups(const std::vector<Row> &rows, int32_t L, i
             }
     }
     std::vector<Group> out;
-    run(best_part, best_how, &out);
+    for (int mask : kParts[best_part])
+        if (mask) run(mask, best_how, &out);
     return out;
 }
 
@@ -309,7 +320,10 @@ static void add_item(SplitPlan &P, const Group &g, const rocket_kernels *k, int3
     P.a.resize(P.a.size() + (size_t)nf * kWave * 4);
     uint32_t *dst = P.a.data() + P.a.size() - (size_t)nf * kWave * 4;
     for (int fr = 0; fr < nf; ++fr)
-        for (int h = 0; h < 2; ++h)
+        for (int h = 0; h < 2; ++h) {
+            // the parts of each dword (frame tap 11 holds zeros)
+            int taps[4], lo[4], hi[4];
+            bool masked = false;
             for (int i = 0; i < 4; ++i) {
                 Kind kind = kZero;
                 int tap = 4 * h + i;
@@ -332,18 +346,18 @@ static void add_item(SplitPlan &P, const Group &g, const rocket_kernels *k, int3
                     if (fr == 3 && h == 0) kind = kW11;
                     tap = 8 + i;
                 }
-                const int c0 = g.variant > 0 ? 2 * h : 0;  // the mask slot's first width
-                for (int m = 0; m < kSplitRows; ++m) {
-                    const uint16_t *p = w[m][tap];
-                    uint32_t v = 0;
-                    if (kind == kW13) v = pair16(p[0], p[2]);
-                    if (kind == kW22) v = pair16(p[1], p[1]);
-                    if (kind == kW11) v = pair16(p[0], p[0]);
-                    if (kind == kMask)
-                        v = pair16(cls[m] == c0 ? kSplitMask : 0u, cls[m] == c0 + 1 ? kSplitMask : 0u);
-                    dst[((size_t)fr * kWave + 32 * h + m) * 4 + i] = v;
-                }
+                masked = masked || kind == kMask;
+                taps[i] = kind == kZero || kind == kMask ? 11 : tap;
+                lo[i] = kind == kW22 ? 1 : 0;
+                hi[i] = kind == kW13 ? 2 : lo[i];
             }
+            const int c0 = g.variant > 0 ? 2 * h : 0;  // the mask slot's first width
+            uint32_t *out = dst + ((size_t)fr * kWave + 32 * h) * 4;
+            for (int m = 0; m < kSplitRows; ++m, out += 4) {
+                for (int i = 0; i < 4; ++i) out[i] = pair16(w[m][taps[i]][lo[i]], w[m][taps[i]][hi[i]]);
+                if (masked) out[3] = pair16(cls[m] == c0 ? kSplitMask : 0u, cls[m] == c0 + 1 ? kSplitMask : 0u);
+            }
+        }
     P.cinit.insert(P.cinit.end(), cinit.begin(), cinit.end());
     P.div_O.insert(P.div_O.end(), div_O.begin(), div_O.end());
     P.items.push_back(it);
@@ -385,26 +399,49 @@ rocket_status build_split_plan(const rocket_kernels *k, int32_t L, SplitPlan *ou
     try {
         SplitPlan P;
         P.L = L;
-        std::map<std::pair<int32_t, bool>, std::vector<Row>> by_dil, fp32_only;
-        for (int32_t i = 0; i < k->n_kernels; ++i)
-            (bias_carries(k, i) ? by_dil : fp32_only)[{k->dilation[i], k->length[i] % 2 == 0}].push_back(
-                Row{i, ell_index_for(k->length[i]), outputs(k, i, L)});
-        std::vector<std::array<int64_t, 3>> bucket;
-        for (int32_t i = 0; i < k->n_kernels; ++i) bucket.push_back({k->dilation[i], k->length[i], k->padding[i]});
-        std::sort(bucket.begin(), bucket.end());
-        P.n_buckets = std::unique(bucket.begin(), bucket.end()) - bucket.begin();
+        // the kernels of a dilation and length parity, those that split items
+        // take apart from the others (dilations are at most kMaxDilation)
+        struct Dil {
+            int32_t d;
+            bool even;
+            std::vector<Row> rows, fp32_only;
+        };
+        int32_t d_max = 0;
+        for (int32_t i = 0; i < k->n_kernels; ++i) d_max = std::max(d_max, k->dilation[i]);
+        std::vector<int32_t> n_of(2 * ((size_t)d_max + 1), 0), at(n_of.size(), -1);
+        for (int32_t i = 0; i < k->n_kernels; ++i) ++n_of[2 * k->dilation[i] + (k->length[i] % 2 == 0)];
+        std::vector<Dil> dils;
+        for (size_t c = 0; c < n_of.size(); ++c) {
+            if (n_of[c] == 0) continue;
+            at[c] = (int32_t)dils.size();
+            dils.push_back(Dil{(int32_t)(c / 2), c % 2 != 0, {}, {}});
+            dils.back().rows.reserve(n_of[c]);
+        }
+        for (int32_t i = 0; i < k->n_kernels; ++i) {
+            Dil &e = dils[at[2 * k->dilation[i] + (k->length[i] % 2 == 0)]];
+            (bias_carries(k, i) ? e.rows : e.fp32_only)
+                .push_back(Row{i, ell_index_for(k->length[i]), (int32_t)outputs(k, i, L), k->bias[i]});
+        }
         // by their own numbers (a total order but for equal kernels), so that a
         // kernel's item, and with it the rounding of its dot products, does not
         // depend on the set's order
         auto before = [&](const Row &x, const Row &y) {
-            if (k->bias[x.k] != k->bias[y.k]) return k->bias[x.k] < k->bias[y.k];
+            if (x.bias != y.bias) return x.bias < y.bias;
             if (k->length[x.k] != k->length[y.k]) return k->length[x.k] < k->length[y.k];
             if (x.O != y.O) return x.O < y.O;
             const float *wx = k->weights + (int64_t)x.k * k->max_len, *wy = k->weights + (int64_t)y.k * k->max_len;
             const auto d = std::mismatch(wx, wx + k->length[x.k], wy);
             return d.first != wx + k->length[x.k] ? *d.first < *d.second : x.k < y.k;
         };
-        for (auto &e : by_dil) std::sort(e.second.begin(), e.second.end(), before);
+        std::vector<int64_t> buckets;
+        for (Dil &e : dils) {
+            buckets.clear();
+            for (const auto *rows : {&e.rows, &e.fp32_only})
+                for (const Row &r : *rows) buckets.push_back((int64_t)r.O * 16 + k->length[r.k]);  // these give the padding
+            std::sort(buckets.begin(), buckets.end());
+            P.n_buckets += std::unique(buckets.begin(), buckets.end()) - buckets.begin();
+            std::sort(e.rows.begin(), e.rows.end(), before);
+        }
         struct Choice {
             int32_t d;
             bool even;
@@ -413,21 +450,21 @@ rocket_status build_split_plan(const rocket_kernels *k, int32_t L, SplitPlan *ou
         };
         std::vector<Choice> all;
         double total = 0.0, gain = 0.0;
-        for (const auto &e : by_dil)
-            for (Group &g : best_groups(e.second, L, e.first.first, e.first.second)) {
+        for (const Dil &e : dils) {
+            for (Group &g : best_groups(e.rows, L, e.d, e.even)) {
                 const double c = fp32_cycles(g, k, L);
                 total += std::min(g.cost, c);
                 P.fp32_cost += c;
                 gain += std::max(0.0, g.cost - c);
-                all.push_back(Choice{e.first.first, e.first.second, std::move(g), c});
+                all.push_back(Choice{e.d, e.even, std::move(g), c});
             }
-        for (const auto &e : fp32_only)
-            for (const Group &g : best_groups(e.second, L, e.first.first, e.first.second)) {
+            for (const Group &g : best_groups(e.fp32_only, L, e.d, e.even)) {
                 P.rest.insert(P.rest.end(), g.slot.begin(), g.slot.end());
                 const double c = fp32_cycles(g, k, L);
                 P.rest_cost += c;
                 P.fp32_cost += c;
             }
+        }
         // short series: all kernels or none (the series-lane layout runs one
         // kind of item), by the total
         if (L <= kSeriesMaxL && !P.rest.empty()) all.clear();

@@ -768,13 +768,21 @@ const void *kernel_fn(int shape, bool mpv) {
     }
 }
 
-template <typename T>
-hipError_t upload(const std::vector<T> &h, T **d) {
-    if (h.empty()) return hipSuccess;
-    hipError_t e = hipMalloc((void **)d, h.size() * sizeof(T));
-    if (e == hipSuccess) e = hipMemcpy(*d, h.data(), h.size() * sizeof(T), hipMemcpyHostToDevice);
-    return e;
-}
+// Copies of host tables in one device allocation (a plan is made of many small
+// ones, and an allocation costs as much as their planning): sized by the first
+// walk over the tables, filled by the second.
+struct TablePool {
+    char *base = nullptr;
+    size_t used = 0;
+    template <typename T>
+    hipError_t add(const std::vector<T> &h, T **d) {
+        const size_t at = used;
+        used += (h.size() * sizeof(T) + 255) / 256 * 256;
+        if (!base || h.empty()) return hipSuccess;
+        *d = reinterpret_cast<T *>(base + at);
+        return hipMemcpy(*d, h.data(), h.size() * sizeof(T), hipMemcpyHostToDevice);
+    }
+};
 
 constexpr int kMaxDevices = 64;
 std::mutex g_lds_mu;
@@ -808,6 +816,7 @@ struct SplitDevice {
     int64_t lds = 0;
     int32_t plane_words = 0;
     bool mpv = false;
+    void *tables = nullptr;  // the allocation that the following point into
     SplitItem *items = nullptr;
     uint32_t *a = nullptr;
     float *cinit = nullptr;
@@ -818,9 +827,7 @@ struct SplitDevice {
 
 void split_destroy(SplitDevice *d) {
     if (!d) return;
-    void *ptrs[] = {d->items, d->a, d->cinit, d->kid, d->order, d->split_begin, d->inv_O, d->div_O};
-    for (void *q : ptrs)
-        if (q) (void)hipFree(q);
+    if (d->tables) (void)hipFree(d->tables);
     delete d;
 }
 
@@ -901,14 +908,22 @@ hipError_t split_create(SplitPlan &&plan, int device, int n_cu, int64_t lds_limi
     d->rows = d->shape == 2 ? 1 : (int)((plane / 4 - kEndZeros) / pitch);
     d->plane_words = (int32_t)(plane / 4);
     d->lds = 2 * plane;
-    hipError_t e = upload(d->host.items, &d->items);
-    if (e == hipSuccess) e = upload(d->host.a, &d->a);
-    if (e == hipSuccess) e = upload(d->host.cinit, &d->cinit);
-    if (e == hipSuccess) e = upload(d->host.kid, &d->kid);
-    if (e == hipSuccess) e = upload(d->host.inv_O, &d->inv_O);
-    if (e == hipSuccess && d->host.L <= kSeriesMaxL) e = upload(d->host.div_O, &d->div_O);
-    if (e == hipSuccess) e = upload(d->host.order, &d->order);
-    if (e == hipSuccess) e = upload(d->host.split_begin, &d->split_begin);
+    TablePool pool;
+    auto walk = [&]() {
+        hipError_t e = pool.add(d->host.items, &d->items);
+        if (e == hipSuccess) e = pool.add(d->host.a, &d->a);
+        if (e == hipSuccess) e = pool.add(d->host.cinit, &d->cinit);
+        if (e == hipSuccess) e = pool.add(d->host.kid, &d->kid);
+        if (e == hipSuccess) e = pool.add(d->host.inv_O, &d->inv_O);
+        if (e == hipSuccess && d->host.L <= kSeriesMaxL) e = pool.add(d->host.div_O, &d->div_O);
+        if (e == hipSuccess) e = pool.add(d->host.order, &d->order);
+        if (e == hipSuccess) e = pool.add(d->host.split_begin, &d->split_begin);
+        return e;
+    };
+    hipError_t e = walk();
+    if (e == hipSuccess) e = hipMalloc(&d->tables, std::max<size_t>(pool.used, 256));
+    pool = TablePool{static_cast<char *>(d->tables)};
+    if (e == hipSuccess) e = walk();
     if (e == hipSuccess) e = allow_lds(device, lds_limit - 256);
     if (e != hipSuccess) {
         split_destroy(d);

@@ -1071,13 +1071,15 @@ extern "C" rocket_status rocket_plan_create_ex(const rocket_kernels *k, int32_t 
     }
     const int32_t K = k->n_kernels;
     p->max_len = k->max_len;
-    if (e == hipSuccess) e = upload_raw(k->length, (size_t)K, &p->d_len);
-    if (e == hipSuccess) e = upload_raw(k->dilation, (size_t)K, &p->d_dil);
-    if (e == hipSuccess) e = upload_raw(k->padding, (size_t)K, &p->d_pad);
-    if (e == hipSuccess) e = upload_raw(k->bias, (size_t)K, &p->d_b);
-    if (e == hipSuccess) e = upload_raw(k->weights, (size_t)K * p->C * k->max_len, &p->d_w);
-    if (e == hipSuccess && p->C > 1) e = upload_raw(k->channel_count, (size_t)K, &p->d_cc);
-    if (e == hipSuccess && p->C > 1) e = upload_raw(k->channel_index, (size_t)K * p->C, &p->d_ci);
+    if (p->direct) {  // only its kernel reads the set as given
+        if (e == hipSuccess) e = upload_raw(k->length, (size_t)K, &p->d_len);
+        if (e == hipSuccess) e = upload_raw(k->dilation, (size_t)K, &p->d_dil);
+        if (e == hipSuccess) e = upload_raw(k->padding, (size_t)K, &p->d_pad);
+        if (e == hipSuccess) e = upload_raw(k->bias, (size_t)K, &p->d_b);
+        if (e == hipSuccess) e = upload_raw(k->weights, (size_t)K * p->C * k->max_len, &p->d_w);
+        if (e == hipSuccess && p->C > 1) e = upload_raw(k->channel_count, (size_t)K, &p->d_cc);
+        if (e == hipSuccess && p->C > 1) e = upload_raw(k->channel_index, (size_t)K * p->C, &p->d_ci);
+    }
     if (!p->direct && fp32_items && e == hipSuccess) e = upload_tables(p, lds);
     if (e != hipSuccess) {
         plan_free_device(p);
