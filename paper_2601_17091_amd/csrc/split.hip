@@ -509,10 +509,11 @@ __global__ __launch_bounds__(BLOCK, MPV ? 2 : 3) void rocket_split_kernel(SplitA
     const int xcd = (int)b & ((1 << a.xcd_shift) - 1);
     const int64_t local = b >> a.xcd_shift;
     const int64_t per_variant = a.groups_per_xcd * a.nsplit;
-    const int variant = a.variants[(int)(local / per_variant)];
+    const int vi = (int)(local / per_variant);
+    const int variant = a.variants[vi];
     const int64_t rest = local % per_variant;
-    const int64_t group = xcd * a.groups_per_xcd + rest / a.nsplit;
-    const int split = (int)(rest % a.nsplit);
+    int64_t group;
+    const int split = group_split(xcd, a.xcd_shift, a.groups_per_xcd, a.nsplit, vi, rest, group);
     const int beg = as_const(a.split_begin)[variant * a.nsplit + split];
     const int n_items = as_const(a.split_begin)[variant * a.nsplit + split + 1] - beg;
     const int64_t first = group * a.rows_per_block;
@@ -682,7 +683,7 @@ __device__ __forceinline__ void run_series_items(int *next_item, int idx, SplitI
 }
 
 constexpr int kSeriesBlock = 256;
-constexpr int kSeriesRounds = 4;  // workgroups per CU a launch splits its items for
+constexpr int kSeriesRounds = 4;  // workgroups per CU that a launch splits its items into
 
 template <bool MPV>
 __global__ __launch_bounds__(kSeriesBlock, MPV ? 2 : 3) void rocket_split_series_kernel(SplitArgs a) {
@@ -737,10 +738,11 @@ __global__ __launch_bounds__(kSeriesBlock, MPV ? 2 : 3) void rocket_split_series
     }
 }
 
-// Workgroup shapes.  The kernel's registers (164, with MPV 204) allow three
-// wavefronts per SIMD (with MPV two), so a CU holds 12 (8): three workgroups
-// of 256 threads with a third of the 160 KB of LDS each, two of 384, or one of
-// 768 for rows that take more than half (with MPV two of 256, one of 512).
+// Workgroup shapes.  The kernel's registers (168, with MPV 205 to 209) allow
+// three wavefronts per SIMD (with MPV two), so a CU holds 12 (8): three
+// workgroups of 256 threads with a third of the 160 KB of LDS each, two of 384,
+// or one of 768 for rows that take more than half (with MPV two of 256, one of
+// 512).
 struct Shape {
     int block;
     int plane;  // bytes of a plane; 0: given at run time
@@ -813,7 +815,7 @@ namespace rocket {
 struct SplitDevice {
     SplitPlan host;
     int shape = 0, rows = 1, n_cu = 0;
-    int64_t lds = 0;
+    int64_t lds = 0, lds_room = 0;
     int32_t plane_words = 0;
     bool mpv = false;
     void *tables = nullptr;  // the allocation that the following point into
@@ -891,6 +893,7 @@ int split_rows_per_block(const SplitDevice *d) { return d->rows; }
 int64_t split_n_items(const SplitDevice *d) { return (int64_t)d->host.items.size(); }
 int64_t split_n_rest(const SplitDevice *d) { return (int64_t)d->host.rest.size(); }
 int64_t split_n_buckets(const SplitDevice *d) { return d->host.n_buckets; }
+int64_t split_lds_room(const SplitDevice *d) { return d->lds_room; }
 bool split_one_per_cu(const SplitDevice *d) { return d->shape == 2; }
 
 hipError_t split_create(SplitPlan &&plan, int device, int n_cu, int64_t lds_limit, bool mpv, SplitDevice **out) {
@@ -924,7 +927,8 @@ hipError_t split_create(SplitPlan &&plan, int device, int n_cu, int64_t lds_limi
     if (e == hipSuccess) e = hipMalloc(&d->tables, std::max<size_t>(pool.used, 256));
     pool = TablePool{static_cast<char *>(d->tables)};
     if (e == hipSuccess) e = walk();
-    if (e == hipSuccess) e = allow_lds(device, lds_limit - 256);
+    d->lds_room = lds_limit - 256;  // the rest for the workgroup's own variables
+    if (e == hipSuccess) e = allow_lds(device, d->lds_room);
     if (e != hipSuccess) {
         split_destroy(d);
         return e;

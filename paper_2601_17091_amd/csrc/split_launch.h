@@ -26,6 +26,8 @@ int split_rows_per_block(const SplitDevice *d);
 int64_t split_n_items(const SplitDevice *d);
 int64_t split_n_rest(const SplitDevice *d);
 int64_t split_n_buckets(const SplitDevice *d);
+// Dynamic LDS that the kernels are allowed.
+int64_t split_lds_room(const SplitDevice *d);
 // Rows above 40 KB: one workgroup per CU.
 bool split_one_per_cu(const SplitDevice *d);
 // Issue cycles per series of the kernels left to fp32 items.

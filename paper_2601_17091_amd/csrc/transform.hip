@@ -1,5 +1,8 @@
-// ROCKET transform on CDNA4 (gfx950): fused MFMA kernel, plain direct
-// kernel, and the HIP-facing half of the C ABI.
+// ROCKET transform on CDNA4 (gfx950): the fp32 kernels (fused MFMA, Toeplitz,
+// series-lane, MINIROCKET, plain direct) and the HIP-facing half of the C ABI.
+// Most kernels of a univariate set run as split items instead (split.hip); the
+// fp32 items here and in tiles.h run what those leave over, multivariate sets,
+// and the sets that split items do not take or would not speed up.
 //
 // Fused kernel (one workgroup = a few series x one split of the work items
 // of one code variant):
@@ -1340,7 +1343,8 @@ static rocket_status launch_groups(const rocket_plan *p, bool series, const floa
     // 1,000, 10,000 (4e10) 126,200 and 123,500; 16 x 16,000, 10,000 (7.5e8) 502
     // and 594; 400 x 16,000, 1,000 (2.4e9) 2,171 and 2,085.
     const double rest_cycles = p->split ? rocket::split_rest_cost(p->split) * (double)n : 0.0;
-    const bool joined = p->split && !p->clamp && rest_cycles < (rocket::split_one_per_cu(p->split) ? 1e9 : 2.5e8);
+    const bool joined = p->split && !p->clamp && rest_cycles < (rocket::split_one_per_cu(p->split) ? 1e9 : 2.5e8) &&
+                        p->lds_bytes <= rocket::split_lds_room(p->split);
     // Toeplitz items, and the fp32 items of a split plan's long calls, run on
     // the plan's side stream, concurrently with the other part: they start
     // after the caller's earlier work and the call ends on the caller's
@@ -1617,11 +1621,13 @@ extern "C" rocket_status rocket_transform_host(const rocket_plan *p, const float
     // default: about 8 batches, so copies have neighbours to overlap with,
     // each within 256 MiB of staging.  Split plans of long rows take 3: a row
     // computes for longer than its features are copied (both grow with the
-    // kernels, only the first with L; they meet near 1,280 samples), so the
-    // ends of launches count for more than the copies left uncovered (1,000 x
-    // 2,000 samples, 10,000 kernels: 5.08 ms in 8 batches, 3.88 in 3; 200 x
-    // 8,000, 5,000 kernels: 3.79 and 2.90; but 3,000 x 300, 8,000 kernels:
-    // 4.79 and 5.79).
+    // kernels, only the first with L).  Times of one shape vary by a third
+    // with the hardware queues that the call's copy streams come to share with
+    // the transform's (a process has four), more than the number of batches
+    // moves them; lowest seen, ms: 1,000 x 2,000 samples, 10,000 kernels 3.5 in
+    // 3 and in 8; 200 x 8,000, 5,000 kernels 2.5 in 3, 3.3 in 8; 1,000 x 1,600
+    // 4.0 and 4.5; 1,000 x 1,280 3.5 and 4.0; 1,000 x 1,000 2.1 and 3.9; 2,000
+    // x 500 4.9 and 4.7; 3,000 x 300, 8,000 kernels 5.8 and 4.8.
     const int64_t parts = p->split && L >= 1280 ? 3 : 8;
     if (B == 0)
         B = std::max<int64_t>(1, std::min<int64_t>((n + parts - 1) / parts, (int64_t)(256 << 20) / ((L + K2) * 4)));

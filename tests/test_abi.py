@@ -162,6 +162,7 @@ def test_transform_validation(lib):
     assert lib.rocket_transform_plan(None, dummy, 1, dummy, None) == rb.ROCKET_ERR_INVALID_ARG
     assert lib.rocket_transform_plan_noalloc(None, dummy, 1, dummy, None) == rb.ROCKET_ERR_INVALID_ARG
     assert lib.rocket_plan_info(None, None) == rb.ROCKET_ERR_INVALID_ARG
+    assert lib.rocket_plan_split_counts(None, None, None) == rb.ROCKET_ERR_INVALID_ARG
     assert lib.rocket_transform_host(None, dummy, 1, dummy, 0, None) == rb.ROCKET_ERR_INVALID_ARG
 
 
