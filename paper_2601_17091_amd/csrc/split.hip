@@ -72,6 +72,7 @@ struct SplitArgs {
     const int32_t *split_begin;
     int32_t nsplit, n_variants;
     int32_t variants[rocket::kSplitVariants];
+    int32_t part_cap, part_even;  // see part_shift
     int32_t xcd_shift;  // as in FusedArgs
     int64_t groups_per_xcd;
     uint32_t blocks;      // workgroups of split items
@@ -427,11 +428,15 @@ __device__ __forceinline__ SplitItem load_split_item(ConstPtr<SplitItem> p) {
 }
 
 // A workgroup of few items deals each of them to its wavefronts in 2^sh parts
-// of its series (rows do not interact), so that no wavefront goes without.
-__device__ __forceinline__ int part_shift(int n_items, int n_rows, int n_waves) {
-    int sh = 0;
-    while (sh < 2 && (n_items << sh) < 2 * n_waves && (1 << sh) < n_rows) ++sh;
-    return sh;
+// of its series (rows do not interact): so that no wavefront goes without, and,
+// for parts of at least kPartWork samples (part_even), to even out two rounds
+// of tasks (a part costs its item's weights again: 931 x 28 samples, 289
+// kernels, 4 items and 3 series a workgroup, 11.2 us whole and 13.4 in parts).
+constexpr int64_t kPartWork = 1024;
+__device__ __forceinline__ int part_shift(int n_items, const SplitArgs &a, int n_waves) {
+    if (a.part_cap == 0) return 0;
+    const int few = a.part_even ? 2 * n_waves : n_waves;
+    return n_items >= few ? 0 : (2 * n_items >= few ? 1 : a.part_cap);
 }
 
 // The tasks (item, part) of one variant: a wavefront's first is its own
@@ -522,7 +527,7 @@ __global__ __launch_bounds__(BLOCK, MPV ? 2 : 3) void rocket_split_kernel(SplitA
     const int64_t grow = a.row0 + first;
     const uint32_t plane = PLANE ? (uint32_t)PLANE : 4u * (uint32_t)a.plane_words;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / rocket::kWave);
-    const int sh = part_shift(n_items, nrows, BLOCK / rocket::kWave);
+    const int sh = part_shift(n_items, a, BLOCK / rocket::kWave);
     const SplitItem it0 =
         load_split_item(as_const(a.items) + as_const(a.order)[beg + min(wave >> sh, n_items - 1)]);
     stage_rows<BLOCK>(a, a.X + grow * a.L, nrows, smem, smem + plane / 4);
@@ -704,7 +709,8 @@ __global__ __launch_bounds__(kSeriesBlock, MPV ? 2 : 3) void rocket_split_series
     const int64_t first = group * rocket::kWave;
     if (n_items == 0 || first >= a.n_rows) return;
     const int n_series = (int)min((int64_t)rocket::kWave, a.n_rows - first);
-    const int sh = n_items < 2 * (kSeriesBlock / rocket::kWave) ? 1 : 0;
+    constexpr int kWaves = kSeriesBlock / rocket::kWave;
+    const int sh = n_items < kWaves || (n_items < 2 * kWaves && a.L * rocket::kSplitTile >= kPartWork) ? 1 : 0;
     const SplitItem it0 =
         load_split_item(as_const(a.items) + as_const(a.order)[beg + min(wave >> sh, n_items - 1)]);
     // stage: lane = series, so that a position's 64 words are written at once
@@ -976,6 +982,8 @@ rocket_status split_launch(const SplitDevice *d, const float *X, int64_t n, int3
     for (int v = kSplitVariants - 1; v >= 0; --v)
         if (sb[(v + 1) * a.nsplit] > sb[v * a.nsplit]) a.variants[a.n_variants++] = v;
     a.rows_per_block = R;
+    a.part_cap = R >= 4 ? 2 : (R >= 2 ? 1 : 0);
+    a.part_even = ((int64_t)R * P.L >> a.part_cap) >= kPartWork ? 1 : 0;
     a.pitch = P.L + kMargin;
     a.plane_words = d->plane_words;
     a.vec4 = (P.L % 4 == 0 && ((uintptr_t)X % 16) == 0) ? 1 : 0;

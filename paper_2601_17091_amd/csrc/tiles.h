@@ -1407,8 +1407,8 @@ __device__ __forceinline__ int group_split(int xcd, int xcd_shift, int64_t group
         group = rest % groups;
         return ((int)(rest / groups) + 5 * vi) & (nsplit - 1);  // nsplit is a power of two
     }
-    group = xcd * groups + rest / nsplit;
-    return (int)(rest % nsplit);
+    group = xcd * groups + (rest >> __builtin_ctz(nsplit));
+    return (int)rest & (nsplit - 1);
 }
 
 // Workgroup = (variant, row group, split).  Workgroup b of the launch's fp32
