@@ -118,14 +118,17 @@ __device__ __forceinline__ void split_words(float x, uint32_t &w0, uint32_t &w1)
 }
 
 // Per-row accumulators of an item, per lane.
-template <bool MPV>
+template <int MPV>
 struct Acc {
     float mn[kRegs];            // running minimum of -y
     uint32_t cnt[kRegs / 2];    // sums of sign masks of rows (2 j, 2 j + 1) in the halves
-    // sums of positive y, one per tile of a block: chains of O / 64 additions,
-    // as in the fp32 items (one chain of O / 32 had up to 7 % more rounding
-    // error, at 16,384 samples)
-    float ps[2][MPV ? kRegs : 1];
+    // sums of positive y in MPV chains, two of them one per tile of a block:
+    // chains of O / 64 additions, as in the fp32 items (one chain of O / 32 had
+    // up to 7 % more rounding error, at 16,384 samples; up to 128 samples it
+    // has no more than the fp32 items, and two cost 5 to 9 % of a call)
+    float ps[MPV == 2 ? 2 : 1][MPV ? kRegs : 1];
+    // the sum of both chains
+    __device__ __forceinline__ float sum(int i) const { return MPV == 2 ? ps[0][i] + ps[MPV == 2 ? 1 : 0][i] : ps[0][i]; }
 };
 
 // The word addresses of one block: LDS bytes of the lane's column in tile 0
@@ -147,7 +150,7 @@ __device__ __forceinline__ v16f mfma(const v4u &a, const v4u &b, const v16f &c) 
 // the words, the MFMAs (small parts first) and the fold.  plane: bytes from
 // plane 0 to plane 1; mask(u): the mask word of tile u (EDGE blocks; others
 // have zeros in its slot).  STRIDE: bytes from one tile's words to the next's.
-template <int V, int NT, bool MPV, bool EDGE, int FIRST, int STRIDE, typename Mask>
+template <int V, int NT, int MPV, bool EDGE, int FIRST, int STRIDE, typename Mask>
 __device__ __forceinline__ void block(const Addr<V> &ad, uint32_t plane, const v4u (&fa)[rocket::kSplitFrags[V]],
                                       const v16f &cinit, const Mask &mask, int h, Acc<MPV> &ac,
                                       const CheckBounds &cb) {
@@ -197,9 +200,9 @@ __device__ __forceinline__ void block(const Addr<V> &ad, uint32_t plane, const v
 #pragma unroll
     for (int i = 0; i < kRegs; ++i) {
         ac.mn[i] = NT == 2 ? fminf(fminf(ac.mn[i], z[0][i]), z[NT - 1][i]) : fminf(ac.mn[i], z[0][i]);
-        if (MPV) {
+        if constexpr (MPV > 0) {
 #pragma unroll
-            for (int u = 0; u < NT; ++u) ac.ps[u][i] += fmaxf(-z[u][i], 0.0f);
+            for (int u = 0; u < NT; ++u) ac.ps[u % MPV][i] += fmaxf(-z[u][i], 0.0f);
         }
     }
 }
@@ -276,7 +279,7 @@ __device__ __forceinline__ void load_fragments(const SplitItem &it, const SplitA
 constexpr int kTileBytes = 4 * rocket::kSplitTile;
 
 // One item over the staged series r0, r0 + r_step, ...
-template <int V, bool MPV>
+template <int V, int MPV>
 __device__ __forceinline__ void run_split_item(const SplitItem &it, const SplitArgs &a, uint32_t lds0, uint32_t plane,
                                                int r0, int r_step, int nrows, float *F0, int lane,
                                                const CheckBounds &cb) {
@@ -313,7 +316,8 @@ __device__ __forceinline__ void run_split_item(const SplitItem &it, const SplitA
 #pragma unroll
         for (int i = 0; i < kRegs; ++i) {
             ac.mn[i] = INFINITY;
-            if (MPV) ac.ps[0][i] = ac.ps[1][i] = 0.0f;
+            if (MPV) ac.ps[0][i] = 0.0f;
+            if constexpr (MPV == 2) ac.ps[1][i] = 0.0f;
         }
 #pragma unroll
         for (int j = 0; j < kRegs / 2; ++j) ac.cnt[j] = 0u;
@@ -378,10 +382,10 @@ __device__ __forceinline__ void run_split_item(const SplitItem &it, const SplitA
         const uint32_t hi = (lo - ((packed + lo) >> 16)) & 0xffffu;
         const uint32_t c = (lane & 2) ? hi : lo;
         float ps = 0.0f;
-        if constexpr (MPV) {
+        if constexpr (MPV > 0) {
             uint32_t p[kRegs];
 #pragma unroll
-            for (int i = 0; i < kRegs; ++i) p[i] = __float_as_uint(ac.ps[0][i] + ac.ps[1][i]);
+            for (int i = 0; i < kRegs; ++i) p[i] = __float_as_uint(ac.sum(i));
             ps = __uint_as_float(tree<OpFadd>(p, lane));
         }
         if (okid >= 0) {
@@ -442,7 +446,7 @@ __device__ __forceinline__ int part_shift(int n_items, const SplitArgs &a, int n
 // The tasks (item, part) of one variant: a wavefront's first is its own
 // number's (it, read by the caller while the series were staged), the others
 // come from the workgroup's counter.
-template <int V, bool MPV>
+template <int V, int MPV>
 __device__ __forceinline__ void run_split_items(int *next_item, int idx, SplitItem it, int beg, int n_items, int sh,
                                                 const SplitArgs &a, uint32_t lds0, uint32_t plane, int nrows, float *F0,
                                                 int lane, const CheckBounds &cb) {
@@ -496,7 +500,7 @@ __device__ __forceinline__ void stage_rows(const SplitArgs &a, const float *X, i
 // fp32 items of q.  BLOCK threads; PLANE: bytes of a plane where fixed (an
 // immediate offset of the LDS reads), 0 where given at run time (rows above
 // 40 KB).
-template <int BLOCK, int PLANE, bool MPV>
+template <int BLOCK, int PLANE, int MPV>
 __global__ __launch_bounds__(BLOCK, MPV ? 2 : 3) void rocket_split_kernel(SplitArgs a, FusedArgs q) {
     extern __shared__ __align__(16) uint32_t smem[];
     __shared__ int next_item;
@@ -505,7 +509,7 @@ __global__ __launch_bounds__(BLOCK, MPV ? 2 : 3) void rocket_split_kernel(SplitA
         GroupWork w;
         float *rows = reinterpret_cast<float *>(smem);
         if (!stage_group<BLOCK>(q, blockIdx.x - a.blocks, rows, &next_item, w)) return;
-        run_variant<false, MPV>(&next_item, w, q, rows + q.halo_lo, q.F + w.grow * (int64_t)q.nf * q.K, lane);
+        run_variant<false, (MPV > 0)>(&next_item, w, q, rows + q.halo_lo, q.F + w.grow * (int64_t)q.nf * q.K, lane);
         return;
     }
     // workgroup b runs on XCD b % 8; every XCD takes its own share of the row
@@ -557,7 +561,7 @@ __global__ __launch_bounds__(BLOCK, MPV ? 2 : 3) void rocket_split_kernel(SplitA
 constexpr int kPosBytes = 4 * rocket::kWave;  // one position of a plane
 constexpr int kSM = rocket::kSplitSeriesMargin;
 
-template <int V, bool MPV>
+template <int V, int MPV>
 __device__ __forceinline__ void run_series_item(const SplitItem &it, const SplitArgs &a, uint32_t lds0, uint32_t plane,
                                                 int64_t series0, int first, int n_series, int lane,
                                                 const CheckBounds &cb) {
@@ -584,7 +588,8 @@ __device__ __forceinline__ void run_series_item(const SplitItem &it, const Split
 #pragma unroll
         for (int i = 0; i < kRegs; ++i) {
             ac.mn[i] = INFINITY;
-            if (MPV) ac.ps[0][i] = ac.ps[1][i] = 0.0f;
+            if (MPV) ac.ps[0][i] = 0.0f;
+            if constexpr (MPV == 2) ac.ps[1][i] = 0.0f;
         }
 #pragma unroll
         for (int j = 0; j < kRegs / 2; ++j) ac.cnt[j] = 0u;
@@ -660,7 +665,7 @@ __device__ __forceinline__ void run_series_item(const SplitItem &it, const Split
                 if (MPV) {
                     f[0] = ppv;
                     f[1] = m;
-                    f[2] = c > 0 ? (ac.ps[0][i] + ac.ps[1][i]) / fc : 0.0f;
+                    f[2] = c > 0 ? ac.sum(i) / fc : 0.0f;
                 } else {
                     *reinterpret_cast<float2 *>(f) = make_float2(ppv, m);
                 }
@@ -671,7 +676,7 @@ __device__ __forceinline__ void run_series_item(const SplitItem &it, const Split
 
 // The tasks of one variant, as run_split_items: items, or where those are few
 // (sh = 1) items x the workgroup's two tiles of 32 series.
-template <int V, bool MPV>
+template <int V, int MPV>
 __device__ __forceinline__ void run_series_items(int *next_item, int idx, SplitItem it, int beg, int n_items, int sh,
                                                  const SplitArgs &a, uint32_t lds0, uint32_t plane, int64_t series0,
                                                  int n_series, int lane, const CheckBounds &cb) {
@@ -690,7 +695,7 @@ __device__ __forceinline__ void run_series_items(int *next_item, int idx, SplitI
 constexpr int kSeriesBlock = 256;
 constexpr int kSeriesRounds = 4;  // workgroups per CU that a launch splits its items into
 
-template <bool MPV>
+template <int MPV>
 __global__ __launch_bounds__(kSeriesBlock, MPV ? 2 : 3) void rocket_split_series_kernel(SplitArgs a) {
     extern __shared__ __align__(16) uint32_t smem[];
     __shared__ int next_item;
@@ -765,14 +770,16 @@ int32_t xcd_shift(int64_t groups) {
     return 5 * groups < 4 * slots ? 0 : kXcdShift;
 }
 
-const void *kernel_fn(int shape, bool mpv) {
-    if (mpv)
-        return shape == 2 ? (const void *)rocket_split_kernel<512, 0, true>
-                          : (const void *)rocket_split_kernel<256, 40704, true>;
+// chains: see Acc (1 up to 128 samples, whose rows never take shape 2).
+const void *kernel_fn(int shape, int chains) {
+    if (chains > 0 && shape == 2) return (const void *)rocket_split_kernel<512, 0, 2>;
+    if (chains > 0)
+        return chains == 1 ? (const void *)rocket_split_kernel<256, 40704, 1>
+                           : (const void *)rocket_split_kernel<256, 40704, 2>;
     switch (shape) {
-        case 0: return (const void *)rocket_split_kernel<256, 26624, false>;
-        case 1: return (const void *)rocket_split_kernel<384, 40704, false>;
-        default: return (const void *)rocket_split_kernel<768, 0, false>;
+        case 0: return (const void *)rocket_split_kernel<256, 26624, 0>;
+        case 1: return (const void *)rocket_split_kernel<384, 40704, 0>;
+        default: return (const void *)rocket_split_kernel<768, 0, 0>;
     }
 }
 
@@ -801,12 +808,12 @@ hipError_t allow_lds(int device, int64_t limit) {
     if (device < 0 || device >= kMaxDevices) return hipErrorInvalidDevice;
     std::lock_guard<std::mutex> lock(g_lds_mu);
     if (g_lds_allowed[device]) return hipSuccess;
-    for (int sel = 0; sel < 6; ++sel) {
-        const hipError_t e = hipFuncSetAttribute(kernel_fn(sel / 2, sel % 2 != 0),
+    for (int sel = 0; sel < 9; ++sel) {
+        const hipError_t e = hipFuncSetAttribute(kernel_fn(sel / 3, sel % 3),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)limit);
         if (e != hipSuccess) return e;
     }
-    for (const void *fn : {(const void *)rocket_split_series_kernel<false>, (const void *)rocket_split_series_kernel<true>}) {
+    for (const void *fn : {(const void *)rocket_split_series_kernel<0>, (const void *)rocket_split_series_kernel<1>}) {
         const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)limit);
         if (e != hipSuccess) return e;
     }
@@ -887,7 +894,7 @@ rocket_status split_launch_series(const SplitDevice *d, const float *X, int64_t 
     a.s_floats = (int64_t)P.kid.size() * s_rows * (d->mpv ? 3 : 2);
     const unsigned nb = (unsigned)(kXcds * a.groups_per_xcd * a.nsplit * a.n_variants);
     void *args[] = {&a};
-    const void *fn = d->mpv ? (const void *)rocket_split_series_kernel<true> : (const void *)rocket_split_series_kernel<false>;
+    const void *fn = d->mpv ? (const void *)rocket_split_series_kernel<1> : (const void *)rocket_split_series_kernel<0>;
     if (hipLaunchKernel(fn, dim3(nb), dim3(kSeriesBlock), args, (size_t)split_series_lds(P.L), s) != hipSuccess ||
         hipGetLastError() != hipSuccess)
         return ROCKET_ERR_HIP;
@@ -1012,7 +1019,7 @@ rocket_status split_launch(const SplitDevice *d, const float *X, int64_t n, int3
             blocks += (uint32_t)(share(q.rows_per_block, &q.xcd_shift, &q.groups_per_xcd) * q.nsplit * q.n_variants);
         }
         void *args[] = {&a, &q};
-        if (hipLaunchKernel(kernel_fn(d->shape, d->mpv), dim3(blocks), dim3(block), args, lds, s) != hipSuccess ||
+        if (hipLaunchKernel(kernel_fn(d->shape, !d->mpv ? 0 : (P.L <= kSeriesMaxL ? 1 : 2)), dim3(blocks), dim3(block), args, lds, s) != hipSuccess ||
             hipGetLastError() != hipSuccess)
             return ROCKET_ERR_HIP;
     }
