@@ -760,16 +760,6 @@ struct Shape {
 };
 constexpr Shape kShapes[2][3] = {{{256, 26624}, {384, 40704}, {768, 0}}, {{256, 40704}, {256, 40704}, {512, 0}}};
 
-// Row groups go to the XCDs in equal shares, unless that would leave a fifth of
-// the chip without work (one series would run on one XCD alone): then the
-// workgroups are dealt to the XCDs one by one.  One series, us: 500 samples,
-// 10,000 kernels 15.3 -> 9.0, 16,000 samples 513 -> 180; with balanced shares
-// (16 and 50 series of 64 to 200 samples) the shares measured 5 % faster.
-int32_t xcd_shift(int64_t groups) {
-    const int64_t slots = (groups + kXcds - 1) / kXcds * kXcds;
-    return 5 * groups < 4 * slots ? 0 : kXcdShift;
-}
-
 // chains: see Acc (1 up to 128 samples, whose rows never take shape 2).
 const void *kernel_fn(int shape, int chains) {
     if (chains > 0 && shape == 2) return (const void *)rocket_split_kernel<512, 0, 2>;

@@ -1395,6 +1395,16 @@ struct GroupWork {
     int64_t grow;   // first series (global row)
 };
 
+// Row groups go to the XCDs in equal shares, unless that would leave a fifth of
+// the chip without work (one series would run on one XCD alone): then the
+// workgroups are dealt to the XCDs one by one.  One series, us: 500 samples,
+// 10,000 kernels 15.3 -> 9.0, 16,000 samples 513 -> 180; with balanced shares
+// (16 and 50 series of 64 to 200 samples) the shares measured 5 % faster.
+inline int32_t xcd_shift(int64_t groups) {
+    const int64_t slots = (groups + kXcds - 1) / kXcds * kXcds;
+    return 5 * groups < 4 * slots ? 0 : kXcdShift;
+}
+
 // The row group and the split of workgroup `rest` of a variant (the vi-th of
 // the launch) in an XCD's share.  In one share of all XCDs (xcd_shift 0) the
 // groups go fastest and each variant starts at another split: the splits that

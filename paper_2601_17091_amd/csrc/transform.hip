@@ -1381,9 +1381,9 @@ static rocket_status launch_groups(const rocket_plan *p, bool series, const floa
             q.row0 = r0;
             q.n_rows = std::min<int64_t>(max_rows, n - r0);
             const int64_t groups_now = (q.n_rows + R - 1) / R;
-            q.xcd_shift = kXcdShift;
-            q.groups_per_xcd = (groups_now + kXcds - 1) / kXcds;
-            const unsigned nb = (unsigned)(kXcds * q.groups_per_xcd * nsplit * q.n_variants);
+            q.xcd_shift = series ? kXcdShift : xcd_shift(groups_now);
+            q.groups_per_xcd = (groups_now + (1 << q.xcd_shift) - 1) >> q.xcd_shift;
+            const unsigned nb = (unsigned)((q.groups_per_xcd << q.xcd_shift) * nsplit * q.n_variants);
             void *args[] = {&q};
             if (hipLaunchKernel(fns[part], dim3(nb), dim3(big ? kBigBlock : kBlock), args, lds, sq) != hipSuccess ||
                 hipGetLastError() != hipSuccess) {
