@@ -370,28 +370,30 @@ static void add_item(SplitPlan &P, const Group &g, const rocket_kernels *k, int3
 static constexpr double kRestMinGain = 0.02;
 // Short series take split items below this share of the fp32 items' cost: 300
 // kernels x 100 samples (0.8) run 5,000 to 100,000 series at 0.79 to 0.91 of
-// the fp32 items' speed, 500 x 128 (0.69) at 1.07 to 1.12, 300 x 64 (0.69) at
-// 1.05 to 1.10.
-static constexpr double kShortGain = 0.78;
-
+// the fp32 items' speed but 1,000 (tiled) at 1.6, 500 x 128 (0.69) 1.07 to 1.24.
+static constexpr double kShortGain = 0.85;
 // Sets of few kernels leave the wavefronts of a split workgroup without items
 // (it stages its series for each of three variants), and their rest is most of
-// the work: below these bounds the fp32 plan of the whole set is the faster one
-// somewhere between 16 and 100,000 series, by up to a quarter.  Speed against
-// that plan at many (1,000) series: 200 kernels x 300 samples (3 items, gain
-// 1.16) 1.12 (0.80); 300 x 500 (6, 1.16) 1.10 (0.91); 500 x 500 (13, 1.26) 1.19
-// (1.03); 1,000 x 4,000 (18, 1.18) 1.15 (1.17).  With MPV (two wavefronts per
-// SIMD): 500 x 500 1.03 (0.79), 1,000 x 2,000 (22, 1.22) 1.04 (1.02, 100 series
-// 0.81), 1,000 x 500 (27, 1.42) 1.12 (0.96), 2,000 x 5,000 (1.27) 1.08 (1.06).
-// Above 10,000 samples any split items pay with many series (150 kernels 1.07,
-// 1,000 kernels 1.05 at 16,000 samples; 200 x 12,000 1.27).
-static constexpr double kSplitMinGain = 1.15, kSplitMinGainMpv = 1.25;
-static constexpr size_t kSplitMinItems = 12, kSplitMinItemsMpv = 20;
+// the work.  Speed against the fp32 plan of the whole set at 100,000 / 1,000 /
+// 100 / 16 series, by model gain: 100 kernels x 2,000 samples (1.03) 1.00 / 0.74
+// / 1.07 / 1.06, 100 x 300 (1.06) 1.10 / 0.84 / 0.98 / 1.12, 150 x 500 (1.07)
+// 1.12 / 0.89 / 1.14 / 1.29, 200 x 300 (1.16) 1.12 / 0.80 / 1.16 / 1.20, 300 x
+// 1,000 (1.11) 1.12 / 0.81 / 1.33 / 1.41, 500 x 500 (1.26) 1.19 / 1.03 / 1.12 /
+// 1.19: the line lies where many series break even; about 1,000 series of the
+// smallest sets stay slower, as their fp32 items run beside split workgroups
+// that are too few to fill the chip.  With MPV (two wavefronts per SIMD) more is
+// needed, and 20 items: 300 x 500 (6 items, 1.16) 0.91 / 0.68 / 0.90, 500 x 500
+// (13, 1.26) 1.03 / 0.79 / 0.89, 1,000 x 2,000 (22, 1.22) 1.04 / 1.02 / 0.81,
+// 1,000 x 500 (27, 1.42) 1.12 / 0.96 / 0.98, 2,000 x 5,000 (1.27) 1.08 / 1.06 /
+// 1.02.  Above 10,000 samples any split items pay with many series (150 kernels
+// 1.07, 1,000 kernels 1.05 at 16,000 samples; 200 x 12,000 1.27).
+static constexpr double kSplitMinGain = 1.04, kSplitMinGainMpv = 1.25;
+static constexpr size_t kSplitMinItemsMpv = 20;
 
 bool split_pays(const SplitPlan &P, bool mpv) {
     if (P.items.empty()) return false;
     if (P.L <= kSeriesMaxL || P.L > 10000) return true;
-    return P.items.size() >= (mpv ? kSplitMinItemsMpv : kSplitMinItems) &&
+    return P.items.size() >= (mpv ? kSplitMinItemsMpv : 1) &&
            P.fp32_cost >= (mpv ? kSplitMinGainMpv : kSplitMinGain) * (P.cost + P.rest_cost);
 }
 
