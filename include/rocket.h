@@ -286,8 +286,8 @@ rocket_status rocket_transform(const float *X_dev, int64_t n, int32_t L, const r
  * (same layout and feature order as rocket_transform_plan; X_host must be
  * finite).  Rows go
  * through the device in batches of batch_rows (0: about n/8 rows, or n/3 for
- * split items on rows of 1,280 samples and more; at most 256 MiB of staging
- * per buffer).  Each
+ * split items on fewer than 2,048 rows of 1,280 samples and more; at most
+ * 256 MiB of staging per buffer).  Each
  * batch's copy in, transform and copy out run on three HIP streams (the
  * caller's stream for the transform, two of the library's own for the
  * copies), double-buffered, so copies overlap the transform of the

@@ -15,7 +15,7 @@ namespace rocket {
 
 // What a 32-column tile costs by variant, an edge tile more, and an item's
 // reductions and stores per series.  The split kernel runs at the card's power
-// limit (its clock falls to 1.7-1.9 GHz), so these are time at the limit in
+// limit (its clock falls to 1.6-1.9 GHz), so these are time at the limit in
 // 2.4 GHz cycles per SIMD: a 32x32x16 MFMA on random data 43, a vector
 // instruction 1.9, an LDS read 4.6 (each measured in a loop on all CUs).
 // Sweeps of the three rates by 10 % and of the edge and item terms from 0 to

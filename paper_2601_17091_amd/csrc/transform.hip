@@ -1619,16 +1619,17 @@ extern "C" rocket_status rocket_transform_host(const rocket_plan *p, const float
     const int64_t K2 = p->f_cols;  // floats per feature row
     int64_t B = batch_rows;
     // default: about 8 batches, so copies have neighbours to overlap with,
-    // each within 256 MiB of staging.  Split plans of long rows take 3: a row
-    // computes for longer than its features are copied (both grow with the
-    // kernels, only the first with L).  Times of one shape vary by a third
+    // each within 256 MiB of staging.  Few long rows of split plans (eighths
+    // of under a row per CU) take 3: a row computes for longer than its
+    // features are copied (both grow with the kernels, only the first with L).  Times of one shape vary by a third
     // with the hardware queues that the call's copy streams come to share with
     // the transform's (a process has four), more than the number of batches
     // moves them; lowest seen, ms: 1,000 x 2,000 samples, 10,000 kernels 3.5 in
     // 3 and in 8; 200 x 8,000, 5,000 kernels 2.5 in 3, 3.3 in 8; 1,000 x 1,600
     // 4.0 and 4.5; 1,000 x 1,280 3.5 and 4.0; 1,000 x 1,000 2.1 and 3.9; 2,000
-    // x 500 4.9 and 4.7; 3,000 x 300, 8,000 kernels 5.8 and 4.8.
-    const int64_t parts = p->split && L >= 1280 ? 3 : 8;
+    // x 500 4.9 and 4.7; 3,000 x 300, 8,000 kernels 5.8 and 4.8; 5,000 x
+    // 1,400, 2,000 kernels 4.0 and 3.6; 91,340 x 1,612, 296 kernels 24 and 18.
+    const int64_t parts = p->split && L >= 1280 && n < 8 * (int64_t)p->n_cu ? 3 : 8;
     if (B == 0)
         B = std::max<int64_t>(1, std::min<int64_t>((n + parts - 1) / parts, (int64_t)(256 << 20) / ((L + K2) * 4)));
     B = std::min(B, n);
